@@ -1366,6 +1366,8 @@ static void run_model(mpip_model* m, const Plan& p, char* w, const NbrBuffers& b
   nk.dt = LD[K - 1].nk_dt; nk.d = LD[K - 1].nk_d;
   nk.msg = nodeK ? (const unsigned short*)fa.msg : nullptr;
   nk.row_ptr = b.row_ptr;
+  nk.capacity = max_edges;
+  nk.status = b.status;
   nk.inv_n = fa.inv_n;
   nk.out_scale = K == 2 ? 1.f : fa.inv_n;
   Node1Args n1;

@@ -360,6 +360,8 @@ template <int C>
 __global__ __launch_bounds__(64 * kN1Waves) __attribute__((amdgpu_waves_per_eu(4))) void k_nodeK(NodeKArgs a) {
   constexpr int MT = C / 16, KC = C / 32;
   __shared__ bf16x8 sDt[MT * KC * 64], sD[MT * KC * 64];
+  // a list that did not fit: its row offsets run past the messages
+  if ((int64_t)a.row_ptr[a.n] > a.capacity || a.status[ST_FLAGS] != 0) return;
   stage_tiles<MT * KC>(sDt, (const bf16x8*)a.dt);
   stage_tiles<MT * KC>(sD, (const bf16x8*)a.d);
   lds_dma_sync();

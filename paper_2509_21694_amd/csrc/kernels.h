@@ -191,6 +191,8 @@ struct NodeKArgs {
   float* A;               // [N][C]: dE/dA / n_avg out
   const unsigned short* msg;   // per-edge BF16 messages [E][C] in receiver-side CSR slots: A_i = inv_n sum msg[e]
   const int32_t* row_ptr;
+  int64_t capacity;       // messages that msg holds
+  const int64_t* status;
   float inv_n;
   float out_scale;        // of dE/dA: 1, or 1/n_avg when d does not hold it
   const float* h;         // [N][nlm][C]: the previous layer's h_0 rows
