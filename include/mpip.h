@@ -313,18 +313,45 @@ mpip_status mpip_coupling_tensor(int32_t l1, int32_t l2, int32_t l3, double* out
 
 #define MPIP_RADIAL_TABLE_INTERVALS 4096
 
-/* The BF16 form's radial table of layer `layer` (1-based), as
- * mpip_model_create builds it: the radial MLP's second hidden layer
+/* The BF16 form's radial table of all hidden units of layer `layer`
+ * (1-based): the radial MLP's second hidden layer
  * a(d) = silu(W2^T silu(W1^T e(d))) (e: Bessel basis times envelope) at the
  * knots d_k = k r_cut / MPIP_RADIAL_TABLE_INTERVALS, in FP64 from the FP32
  * weights.  Host only, no GPU needed.  out: host
  * [MPIP_RADIAL_TABLE_INTERVALS][radial_hidden] words; word (k, h) holds
  * BF16 a_h(d_k) in bits 0..15 and BF16 (a_h(d_k+1) - a_h(d_k)) in bits
- * 16..31.  The specialised layers interpolate it linearly in d and take
- * the interval's slope as da/dd.  EINVAL for bad hparams, weight count or
- * layer. */
+ * 16..31, interpolated linearly in d, with the interval's slope as da/dd.
+ * The kernels read this table where a layer's radial functions need all
+ * hidden units, and a table of fewer directions of a(d) otherwise
+ * (mpip_radial_operands says which).  EINVAL for bad hparams, weight count
+ * or layer. */
 mpip_status mpip_radial_table(const mpip_hparams* hp, const float* weights_host, size_t n, int32_t layer,
                               uint32_t* out);
+
+/* What the kernels read of the radial functions of layer `layer` (1-based),
+ * decoded from the arrays that mpip_model_create uploads (for checks).  Host
+ * only, no GPU needed.  The functions b(d) = turn^T a(d) are polynomials in
+ * tau = d intervals / r_cut - k on interval k; the radial coefficients are
+ * b(d) weights.  set:
+ *   0, 1  the products with W3 (1: as the last layer evaluated, paths to
+ *         scalars only).  Columns: BF16 form the coefficients (l1, l3, |m|) of
+ *         the edge frame, |m| <= min(l1, l3) (l_max = 1: |m| = 0 only), each
+ *         sum over l2 of sqrt(2 l2 + 1) C[m, 0, m] W3[path], in that order;
+ *         FP32 form the paths; times channels;
+ *   2     layer 1 with up to 4 species, 64 or 128 channels and a second layer:
+ *         the functions of its node arrays (no weights).
+ * info always; turn [radial_hidden][functions], table
+ * [intervals][functions][4] (orders 0..3 in tau) and weights
+ * [functions][columns] where not null.  EINVAL for bad arguments. */
+typedef struct {
+  int32_t functions;   /* of d                                                        */
+  int32_t directions;  /* 1: directions of a(d), 0: the hidden units themselves       */
+  int32_t intervals;   /* of [0, r_cut]                                               */
+  int32_t columns;     /* of weights                                                  */
+} mpip_radial_info;
+mpip_status mpip_radial_operands(const mpip_hparams* hp, const float* weights_host, size_t n, int32_t layer,
+                                 mpip_precision prec, int32_t set, mpip_radial_info* info, double* turn,
+                                 float* table, double* weights);
 
 /* Molecular dynamics on the device around mpip_evaluate (the MD runs of
  * the results section use Langevin dynamics).  Each of n_steps steps is the

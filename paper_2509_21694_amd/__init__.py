@@ -66,6 +66,11 @@ class MdParamsC(ctypes.Structure):
                 ("temperature", ctypes.c_double), ("seed", ctypes.c_uint64), ("skin", ctypes.c_double)]
 
 
+class RadialInfoC(ctypes.Structure):
+    _fields_ = [("functions", ctypes.c_int32), ("directions", ctypes.c_int32), ("intervals", ctypes.c_int32),
+                ("columns", ctypes.c_int32)]
+
+
 def _load():
     if not os.path.exists(LIB_PATH):
         raise ImportError(f"{LIB_PATH} is not built; run `python paper_2509_21694_amd/build.py`")
@@ -97,6 +102,9 @@ def _load():
     lib.mpip_coupling_tensor.restype = I32
     lib.mpip_radial_table.argtypes = [P(HParamsC), P(ctypes.c_float), SZ, I32, P(ctypes.c_uint32)]
     lib.mpip_radial_table.restype = I32
+    lib.mpip_radial_operands.argtypes = [P(HParamsC), P(ctypes.c_float), SZ, I32, I32, I32, P(RadialInfoC),
+                                         P(ctypes.c_double), P(ctypes.c_float), P(ctypes.c_double)]
+    lib.mpip_radial_operands.restype = I32
     lib.mpip_timing_enable.argtypes = [V, I32]
     lib.mpip_timing_enable.restype = I32
     lib.mpip_timing_read.argtypes = [V, P(TimingC)]
@@ -137,8 +145,8 @@ lib = _load()
 
 EXPORTED = ["mpip_weights_count", "mpip_model_create", "mpip_model_destroy", "mpip_workspace_size",
             "mpip_evaluate", "mpip_workspace_status", "mpip_neighbor_workspace_size",
-            "mpip_neighbor_list", "mpip_coupling_tensor", "mpip_radial_table", "mpip_timing_enable",
-            "mpip_timing_read",
+            "mpip_neighbor_list", "mpip_coupling_tensor", "mpip_radial_table", "mpip_radial_operands",
+            "mpip_timing_enable", "mpip_timing_read",
             "mpip_slab_workspace_size", "mpip_slab_share", "mpip_accumulate_rows",
             "mpip_batch_workspace_size", "mpip_evaluate_batch", "mpip_md_workspace_size", "mpip_md_run",
             "mpip_partitioned_workspace_size", "mpip_evaluate_partitioned", "mpip_bfs_share_workspace_size",
@@ -173,13 +181,33 @@ RADIAL_TABLE_INTERVALS = 4096
 
 
 def radial_table(hp, weights: np.ndarray, layer: int) -> np.ndarray:
-    """The BF16 form's radial table of one layer: uint32 [4096, radial_hidden]
+    """The BF16 form's radial table of all hidden units of one layer: uint32 [4096, radial_hidden]
     (low half BF16 a(d_k), high half BF16 a(d_k+1) - a(d_k))."""
     w = np.ascontiguousarray(weights, dtype=np.float32)
     out = np.zeros((RADIAL_TABLE_INTERVALS, hp.radial_hidden), dtype=np.uint32)
     _check(lib.mpip_radial_table(ctypes.byref(hparams_c(hp)), w.ctypes.data_as(ctypes.POINTER(ctypes.c_float)),
                                  w.size, int(layer), out.ctypes.data_as(ctypes.POINTER(ctypes.c_uint32))))
     return out
+
+
+def radial_operands(hp, weights: np.ndarray, layer: int, precision, set: int):
+    """What the kernels read of a layer's radial functions (mpip_radial_operands):
+    (directions, turn [hidden, functions], table [intervals, functions, 4],
+    weights [functions, columns])."""
+    w = np.ascontiguousarray(weights, dtype=np.float32)
+    info, hpc = RadialInfoC(), hparams_c(hp)
+
+    def call(*out):
+        _check(lib.mpip_radial_operands(ctypes.byref(hpc), w.ctypes.data_as(ctypes.POINTER(ctypes.c_float)), w.size,
+                                        int(layer), PRECISIONS[precision], int(set), ctypes.byref(info), *out))
+
+    call(None, None, None)
+    turn = np.zeros((hp.radial_hidden, info.functions))
+    table = np.zeros((info.intervals, info.functions, 4), dtype=np.float32)
+    wts = np.zeros((info.functions, info.columns))
+    call(turn.ctypes.data_as(ctypes.POINTER(ctypes.c_double)), table.ctypes.data_as(ctypes.POINTER(ctypes.c_float)),
+         wts.ctypes.data_as(ctypes.POINTER(ctypes.c_double)))
+    return bool(info.directions), turn, table, wts
 
 
 def _system(positions, species, cell, pbc, n_owned) -> SystemC:

@@ -437,6 +437,137 @@ std::vector<float> radial_table32(Eval&& eval, int H, double rc) {
   return t;
 }
 
+// V^T of an [H][cols] matrix
+std::vector<double> turned(const std::vector<double>& V, int H, const std::vector<double>& w, int cols) {
+  std::vector<double> o((size_t)H * cols, 0.0);
+  for (int h = 0; h < H; ++h)
+    for (int k = 0; k < H; ++k) {
+      const double v = V[(size_t)h * H + k];
+      for (int c = 0; c < cols; ++c) o[(size_t)k * cols + c] += v * w[(size_t)h * cols + c];
+    }
+  return o;
+}
+
+// The radial functions of a layer as its kernels read them (LayerDev), every
+// table with a row of zeros at its end
+struct RadialHost {
+  std::vector<double> V;   // directions of the products with W3 (comp)
+  int comp, kh1;
+  int rn = kRadTab, crn = kRadTab;             // intervals
+  std::vector<uint32_t> rtab, crtab;           // BF16 form
+  std::vector<float> rtab32, crtab32;          // FP32 form
+};
+RadialHost radial_host(RadialHidden& rad, bool bf, bool first) {
+  const int H = rad.H;
+  const RadialBasis basis = radial_basis(rad, bf);
+  RadialHost r;
+  r.V = basis.V;
+  r.comp = basis.ok ? 1 : 0;
+  r.kh1 = basis.ok32 && first ? 32 : H;
+  if (bf) {
+    if (!r.comp || (first && r.kh1 == H)) {
+      r.rtab = radial_table(rad.W1, rad.W2, rad.nb, H, rad.rc, rad.p);
+      r.rtab.resize(r.rtab.size() + H, 0u);
+    }
+    if (r.comp) r.crtab = radial_table_comp(rad, r.V, false);
+    if (r.kh1 == 32) r.rtab = radial_table_comp(rad, r.V, true);
+    return r;
+  }
+  auto table = [&](auto&& eval, int count, int* n) {
+    std::vector<float> t = radial_table32(eval, count, rad.rc);
+    *n = (int)(t.size() / (4 * (size_t)count));
+    t.resize(t.size() + 4 * (size_t)count, 0.f);
+    return t;
+  };
+  // the species-factorised first layer reads all of a(d)
+  if (!r.comp || first) r.rtab32 = table(rad, H, &r.rn);
+  r.crn = r.rn;
+  if (!r.comp) return r;
+  std::vector<double> a(H), da(H);
+  r.crtab32 = table(
+      [&](double x, double* b, double* db) {
+        rad(x, a.data(), da.data());
+        for (int k = 0; k < 48; ++k) {
+          b[k] = db[k] = 0.0;
+          for (int h = 0; h < H; ++h) {
+            b[k] += r.V[(size_t)h * H + k] * a[h];
+            db[k] += r.V[(size_t)h * H + k] * da[h];
+          }
+        }
+      },
+      48, &r.crn);
+  return r;
+}
+
+// W3 of k_layer.hip (LayerDev::wl): what its MFMA rows multiply, [hidden][slot][channel].
+// BF16: the (l1, l3, |m|) coefficients in the order of Coefs (at l_max = 1 one
+// per (l1, l3)), FP32: the paths.  kc: sqrt(2 l2 + 1) C_p[m, 0, m], the
+// couplings in the edge frame, [path][|m| 3].
+bool layer_weights(const std::vector<Path>& paths, const std::vector<int>& live, const float* W3, int H, int C, int L,
+                   bool bf, std::vector<double>& kc, std::vector<double>& ws, int& NS, std::string* why) {
+  const int NP = (int)live.size(), PC = (int)paths.size() * C;
+  kc.assign((size_t)NP * 3, 0.0);
+  int LI = 0, LO = 0;
+  for (int pi = 0; pi < NP; ++pi) {
+    const Path& pp = paths[live[pi]];
+    LI = std::max(LI, pp.l1);
+    LO = std::max(LO, pp.l3);
+    const int n2 = 2 * pp.l2 + 1, n3 = 2 * pp.l3 + 1;
+    std::vector<double> tmp((size_t)(2 * pp.l1 + 1) * n2 * n3);
+    if (!coupling_tensor(pp.l1, pp.l2, pp.l3, tmp.data())) { *why = "coupling"; return false; }
+    for (int m1 = -pp.l1; m1 <= pp.l1; ++m1)
+      for (int m3 = -pp.l3; m3 <= pp.l3; ++m3) {
+        const double v = std::sqrt((double)n2) * tmp[((m1 + pp.l1) * n2 + pp.l2) * n3 + m3 + pp.l3];
+        if (m1 != m3 && std::fabs(v) > 1e-12) { *why = "coupling not diagonal along z"; return false; }
+        if (m1 == m3 && m1 >= 0) kc[(size_t)pi * 3 + m1] = v;
+      }
+  }
+  std::vector<std::vector<double>> slots;
+  if (bf) {
+    for (int l1 = 0; l1 <= LI; ++l1)
+      for (int l3 = 0; l3 <= LO; ++l3)
+        for (int am = 0; am <= (L == 1 ? 0 : std::min(l1, l3)); ++am) {
+          std::vector<double> w((size_t)NP, 0.0);
+          for (int pi = 0; pi < NP; ++pi)
+            if (paths[live[pi]].l1 == l1 && paths[live[pi]].l3 == l3) w[pi] = kc[(size_t)pi * 3 + am];
+          slots.push_back(w);
+        }
+  } else {
+    for (int pi = 0; pi < NP; ++pi) {
+      slots.push_back(std::vector<double>((size_t)NP, 0.0));
+      slots.back()[pi] = 1.0;
+    }
+  }
+  NS = (int)slots.size();
+  ws.assign((size_t)H * NS * C, 0.0);
+  for (int h = 0; h < H; ++h)
+    for (int sl = 0; sl < NS; ++sl)
+      for (int pi = 0; pi < NP; ++pi)
+        if (slots[sl][pi] != 0.0)
+          for (int c = 0; c < C; ++c)
+            ws[((size_t)h * NS + sl) * C + c] += slots[sl][pi] * (double)W3[(size_t)h * PC + live[pi] * C + c];
+  return true;
+}
+// its operands: form's rounding, directions, MFMA tiles
+std::vector<uint16_t> layer_operands(std::vector<double> ws, int NS, int C, bool bf, RadialHidden& rad,
+                                     const RadialHost& r) {
+  const int H = rad.H, ncol = NS * C, nt = hid_tiles(bf, r.comp);
+  if (bf) round_columns(ws, ncol, rad);   // whichever way it is multiplied
+  if (r.comp) ws = turned(r.V, H, ws, ncol);
+  std::vector<uint16_t> wl((size_t)(C / 16) * NS * nt * 64 * 8);
+  for (int o = 0; o < (C / 16) * NS; ++o)
+    for (int q = 0; q < nt; ++q)
+      for (int lane = 0; lane < 64; ++lane)
+        for (int j = 0; j < 8; ++j) {
+          const int quad = o / NS, rho = lane & 15, it = 4 * (o % NS) + rho % 4;
+          const int c = 16 * quad + 4 * (rho / 4) + it / NS;
+          int h, part;
+          hid_slot(bf, r.comp, q, lane >> 4, j, h, part);
+          wl[(((size_t)o * nt + q) * 64 + lane) * 8 + j] = bf_part(ws[(size_t)h * ncol + (size_t)(it % NS) * C + c], part);
+        }
+  return wl;
+}
+
 bool valid_hp(const mpip_hparams* hp, std::string* why) {
   if (!hp) { *why = "null hparams"; return false; }
   if (hp->n_species < 1 || hp->n_species > 64) { *why = "n_species must be in 1..64"; return false; }
@@ -597,21 +728,97 @@ mpip_status mpip_coupling_tensor(int32_t l1, int32_t l2, int32_t l3, double* out
   return MPIP_OK;
 }
 
-mpip_status mpip_radial_table(const mpip_hparams* hp, const float* w, size_t n, int32_t layer, uint32_t* out) {
-  std::string why;
-  if (!valid_hp(hp, &why)) return fail(MPIP_EINVAL, why);
-  if (!w || !out) return fail(MPIP_EINVAL, "null weights or output");
-  if (n != count_weights(*hp)) return fail(MPIP_EINVAL, "weight count does not match the hyper-parameters");
-  if (layer < 1 || layer > hp->n_layers) return fail(MPIP_EINVAL, "no such layer");
-  // the layer's W1 and W2 in the weight blob (the order mpip_model_create reads)
+// W1, W2 and W3 of a layer in the weight blob (the order mpip_model_create reads)
+static const float* radial_weights(const mpip_hparams* hp, const float* w, int32_t layer) {
   const size_t C = hp->channels, H = hp->radial_hidden, nb = hp->n_basis, L = hp->l_max, S = hp->n_species;
   size_t off = S * C;
   for (int t = 1; t < layer; ++t)
     off += ((t == 1) ? 1 : (L + 1)) * C * C + nb * H + H * H + H * n_paths_stored(t, (int)L) * C +
            C * C * (1 + L) + L * C * C;
-  off += ((layer == 1) ? 1 : (L + 1)) * C * C;
-  const std::vector<uint32_t> t = radial_table(w + off, w + off + nb * H, (int)nb, (int)H, hp->r_cut, hp->envelope_p);
+  return w + off + ((layer == 1) ? 1 : (L + 1)) * C * C;
+}
+static mpip_status check_radial(const mpip_hparams* hp, const float* w, size_t n, int32_t layer) {
+  std::string why;
+  if (!valid_hp(hp, &why)) return fail(MPIP_EINVAL, why);
+  if (!w) return fail(MPIP_EINVAL, "null weights");
+  if (n != count_weights(*hp)) return fail(MPIP_EINVAL, "weight count does not match the hyper-parameters");
+  if (layer < 1 || layer > hp->n_layers) return fail(MPIP_EINVAL, "no such layer");
+  return MPIP_OK;
+}
+
+mpip_status mpip_radial_table(const mpip_hparams* hp, const float* w, size_t n, int32_t layer, uint32_t* out) {
+  const mpip_status st = check_radial(hp, w, n, layer);
+  if (st != MPIP_OK) return st;
+  if (!out) return fail(MPIP_EINVAL, "null output");
+  const int H = hp->radial_hidden, nb = hp->n_basis;
+  const float* W1 = radial_weights(hp, w, layer);
+  const std::vector<uint32_t> t = radial_table(W1, W1 + (size_t)nb * H, nb, H, hp->r_cut, hp->envelope_p);
   std::memcpy(out, t.data(), t.size() * sizeof(uint32_t));
+  return MPIP_OK;
+}
+
+mpip_status mpip_radial_operands(const mpip_hparams* hp, const float* w, size_t n, int32_t layer, mpip_precision prec,
+                                 int32_t set, mpip_radial_info* info, double* turn, float* table, double* weights) {
+  const mpip_status st = check_radial(hp, w, n, layer);
+  if (st != MPIP_OK) return st;
+  if (prec != MPIP_FP32 && prec != MPIP_BF16_MIXED) return fail(MPIP_EINVAL, "bad precision");
+  if (set < 0 || set > 2 || (set == 2 && layer != 1)) return fail(MPIP_EINVAL, "no such set");
+  if (!info) return fail(MPIP_EINVAL, "null info");
+  const int C = hp->channels, H = hp->radial_hidden, nb = hp->n_basis, L = hp->l_max;
+  const bool bf = prec == MPIP_BF16_MIXED;
+  const float* W1 = radial_weights(hp, w, layer);
+  const float *W2 = W1 + (size_t)nb * H, *W3 = W2 + (size_t)H * H;
+  RadialHidden rad(W1, W2, nb, H, hp->r_cut, hp->envelope_p);
+  const RadialHost r = radial_host(rad, bf, layer == 1);
+  const std::vector<Path> paths = layer_paths(layer, L);
+  std::vector<int> live;
+  for (int k = 0; k < (int)paths.size(); ++k)
+    if (set == 0 || paths[k].l3 == 0) live.push_back(k);
+  std::vector<double> kc, ws;
+  int NS = 0;
+  std::string why;
+  if (!layer_weights(paths, live, W3, H, C, L, bf, kc, ws, NS, &why)) return fail(MPIP_EINVAL, why);
+  const bool dir = set == 2 ? r.kh1 == 32 : r.comp != 0;
+  const int nf = set == 2 ? r.kh1 : r.comp ? (bf ? 24 : 48) : H;
+  info->functions = nf;
+  info->directions = dir ? 1 : 0;
+  info->intervals = bf ? kRadTab : (set == 2 ? r.rn : r.crn);
+  info->columns = set == 2 ? 0 : NS * C;
+  if (turn)
+    for (int h = 0; h < H; ++h)
+      for (int k = 0; k < nf; ++k) turn[(size_t)h * nf + k] = dir ? r.V[(size_t)h * H + k] : (h == k ? 1.0 : 0.0);
+  if (table)
+    for (int k = 0; k < info->intervals; ++k)
+      for (int f = 0; f < nf; ++f) {
+        float* c = table + ((size_t)k * nf + f) * 4;
+        if (!bf) {
+          std::memcpy(c, &(set == 2 || !r.comp ? r.rtab32 : r.crtab32)[((size_t)k * nf + f) * 4], 4 * sizeof(float));
+          continue;
+        }
+        // interval rows of 64 hidden units, 32 directions, or 24 as 8 words a lane group
+        const uint32_t u = set == 2 || !dir ? r.rtab[(size_t)k * nf + f] : r.crtab[(size_t)k * 32 + 8 * (f % 4) + f / 4];
+        c[1] = bf2f((uint16_t)(u >> 16));
+        c[0] = bf2f((uint16_t)u) - (dir ? 0.5f * c[1] : 0.f);
+        c[2] = c[3] = 0.f;
+      }
+  if (weights && set != 2) {
+    const std::vector<uint16_t> wl = layer_operands(ws, NS, C, bf, rad, r);
+    const int nt = hid_tiles(bf, r.comp), ncol = NS * C;
+    std::vector<uint8_t> seen((size_t)nf * ncol * 3, 0);   // a part may be held in several slots
+    std::fill(weights, weights + (size_t)nf * ncol, 0.0);
+    for (int o = 0; o < (C / 16) * NS; ++o)
+      for (int q = 0; q < nt; ++q)
+        for (int lane = 0; lane < 64; ++lane)
+          for (int j = 0; j < 8; ++j) {
+            const int rho = lane & 15, it = 4 * (o % NS) + rho % 4;
+            const size_t col = (size_t)(it % NS) * C + 16 * (o / NS) + 4 * (rho / 4) + it / NS;
+            int h, part;
+            hid_slot(bf, r.comp, q, lane >> 4, j, h, part);
+            uint8_t& s = seen[((size_t)h * ncol + col) * 3 + part];
+            if (!s) weights[(size_t)h * ncol + col] += bf2f(wl[(((size_t)o * nt + q) * 64 + lane) * 8 + j]);
+            s = 1;
+          }
+  }
   return MPIP_OK;
 }
 
@@ -723,65 +930,22 @@ mpip_status mpip_model_create(const mpip_hparams* hp, const float* w, size_t n, 
       };
       const int KC64 = bf ? 2 : 16;
       auto bfr = [&](float w) { return bf ? bf2f(f2bf(w)) : w; };   // a weight as the form holds it
-      d.rtab = nullptr;
-      d.rtab32 = nullptr;
-      d.kc[0] = d.kc[1] = nullptr;
-      d.rn = d.crn = kRadTab;
       RadialHidden rad(x.W1, x.W2, nb, H, hp->r_cut, hp->envelope_p);
-      const RadialBasis basis = radial_basis(rad, bf);
-      d.comp = basis.ok ? 1 : 0;
-      d.kh1 = basis.ok32 && t == 1 ? 32 : H;
-      const void* tp;
-      if (!bf) {
-        auto put = [&](auto&& eval, int count, const float4** dst, int* rn) -> mpip_status {
-          std::vector<float> tab = radial_table32(eval, count, hp->r_cut);
-          *rn = (int)(tab.size() / (4 * (size_t)count));
-          tab.resize(tab.size() + 4 * (size_t)count, 0.f);   // a zero row for tail lanes
-          const mpip_status r = upload(m, tab, &tp);
-          *dst = (const float4*)tp;
-          return r;
-        };
-        // the species-factorised first layer reads all of a(d)
-        if ((!basis.ok || t == 1) && (st = put(rad, H, &d.rtab32, &d.rn)) != MPIP_OK) goto done;
-        d.crtab32 = d.rtab32;
-        d.crn = d.rn;
-        std::vector<double> a(H), da(H);
-        auto eval = [&](double xx, double* b, double* db) {
-          rad(xx, a.data(), da.data());
-          for (int k = 0; k < 48; ++k) {
-            b[k] = db[k] = 0.0;
-            for (int h = 0; h < H; ++h) {
-              b[k] += basis.V[(size_t)h * H + k] * a[h];
-              db[k] += basis.V[(size_t)h * H + k] * da[h];
-            }
-          }
-        };
-        if (basis.ok && (st = put(eval, 48, &d.crtab32, &d.crn)) != MPIP_OK) goto done;
-      } else {
-        auto put = [&](std::vector<uint32_t> tab, const uint32_t** dst) -> mpip_status {
-          const mpip_status r = upload(m, tab, &tp);
-          *dst = (const uint32_t*)tp;
-          return r;
-        };
-        if (!basis.ok || (t == 1 && d.kh1 == H)) {
-          std::vector<uint32_t> tab = radial_table(x.W1, x.W2, nb, H, hp->r_cut, hp->envelope_p);
-          tab.resize(tab.size() + H, 0u);   // a zero row for tail lanes
-          if ((st = put(tab, &d.rtab)) != MPIP_OK) goto done;
-        }
-        d.crtab = d.rtab;
-        if (basis.ok && (st = put(radial_table_comp(rad, basis.V, false), &d.crtab)) != MPIP_OK) goto done;
-        if (d.kh1 == 32 && (st = put(radial_table_comp(rad, basis.V, true), &d.rtab)) != MPIP_OK) goto done;
-      }
-      // V^T of an [H][cols] matrix
-      auto to_basis = [&](const std::vector<double>& w, int cols) {
-        std::vector<double> o((size_t)H * cols, 0.0);
-        for (int h = 0; h < H; ++h)
-          for (int k = 0; k < H; ++k) {
-            const double v = basis.V[(size_t)h * H + k];
-            for (int c = 0; c < cols; ++c) o[(size_t)k * cols + c] += v * w[(size_t)h * cols + c];
-          }
-        return o;
+      const RadialHost rh = radial_host(rad, bf, t == 1);
+      d.comp = rh.comp;
+      d.kh1 = rh.kh1;
+      d.rn = rh.rn;
+      d.crn = rh.crn;
+      d.kc[0] = d.kc[1] = nullptr;
+      auto put = [&](const auto& v, const auto** dst) -> mpip_status {
+        const void* p = nullptr;
+        const mpip_status r = v.empty() ? MPIP_OK : upload(m, v, &p);
+        *dst = static_cast<std::remove_reference_t<decltype(*dst)>>(p);
+        return r;
       };
+      if ((st = put(rh.rtab, &d.rtab)) != MPIP_OK || (st = put(rh.crtab, &d.crtab)) != MPIP_OK ||
+          (st = put(rh.rtab32, &d.rtab32)) != MPIP_OK || (st = put(rh.crtab32, &d.crtab32)) != MPIP_OK) goto done;
+      if (!rh.comp) { d.crtab = d.rtab; d.crtab32 = d.rtab32; }
       for (int role = 0; role < 2; ++role) {
         const std::vector<int>& lv = live[role];
         const int NPl = (int)lv.size();
@@ -804,66 +968,11 @@ mpip_status mpip_model_create(const mpip_hparams* hp, const float* w, size_t n, 
         const void* cgp;
         if ((st = upload(m, cgv, &cgp)) != MPIP_OK) goto done;
         d.cg[role] = (const float*)cgp;
-        // k_layer.hip: the couplings in the edge frame, sqrt(2 l2 + 1) C_p[m, 0, m]
-        std::vector<double> kcv((size_t)NPl * 3, 0.0);
-        for (int pi = 0; pi < NPl; ++pi) {
-          const Path& pp = stored[lv[pi]];
-          const int n2 = 2 * pp.l2 + 1, n3 = 2 * pp.l3 + 1;
-          std::vector<double> tmp((size_t)(2 * pp.l1 + 1) * n2 * n3);
-          if (!coupling_tensor(pp.l1, pp.l2, pp.l3, tmp.data())) { st = fail(MPIP_EINVAL, "coupling"); goto done; }
-          for (int m1 = -pp.l1; m1 <= pp.l1; ++m1)
-            for (int m3 = -pp.l3; m3 <= pp.l3; ++m3) {
-              const double v = std::sqrt((double)n2) * tmp[((m1 + pp.l1) * n2 + pp.l2) * n3 + m3 + pp.l3];
-              if (m1 != m3 && std::fabs(v) > 1e-12) { st = fail(MPIP_EINVAL, "coupling not diagonal along z"); goto done; }
-              if (m1 == m3 && m1 >= 0) kcv[(size_t)pi * 3 + m1] = v;
-            }
-        }
-        // MFMA rows: BF16 the (l1, l3, |m|) coefficients in the order of k_layer.hip's Coefs
-        // (at l_max = 1 one per (l1, l3)), FP32 the paths
-        std::vector<std::vector<double>> slots;
-        if (bf) {
-          const int LI = t == 1 ? 0 : L, LO = role == 1 ? 0 : L;
-          for (int l1 = 0; l1 <= LI; ++l1)
-            for (int l3 = 0; l3 <= LO; ++l3)
-              for (int am = 0; am <= (L == 1 ? 0 : std::min(l1, l3)); ++am) {
-                std::vector<double> w((size_t)NPl, 0.0);
-                for (int pi = 0; pi < NPl; ++pi)
-                  if (stored[lv[pi]].l1 == l1 && stored[lv[pi]].l3 == l3) w[pi] = kcv[(size_t)pi * 3 + am];
-                slots.push_back(w);
-              }
-        } else {
-          for (int pi = 0; pi < NPl; ++pi) {
-            std::vector<double> w((size_t)NPl, 0.0);
-            w[pi] = 1.0;
-            slots.push_back(w);
-          }
-          std::vector<float> v(kcv.begin(), kcv.end());
-          if ((st = upload(m, v, &cgp)) != MPIP_OK) goto done;
-          d.kc[role] = (const float*)cgp;
-        }
-        const int NS = (int)slots.size(), ncol = NS * C;
-        std::vector<double> ws((size_t)H * ncol, 0.0);   // [hidden][slot][channel]
-        for (int h = 0; h < H; ++h)
-          for (size_t sl = 0; sl < slots.size(); ++sl)
-            for (int pi = 0; pi < NPl; ++pi)
-              if (slots[sl][pi] != 0.0)
-                for (int c = 0; c < C; ++c)
-                  ws[(size_t)h * ncol + sl * C + c] += slots[sl][pi] * (double)W3(h, lv[pi] * C + c);
-        // the BF16 form's W3, whichever way it is multiplied
-        if (bf) round_columns(ws, ncol, rad);
-        if (d.comp) ws = to_basis(ws, ncol);
-        const int nt = hid_tiles(bf, d.comp);
-        std::vector<uint16_t> wl((size_t)(C / 16) * NS * nt * 64 * 8);
-        for (int o = 0; o < (C / 16) * NS; ++o)
-          for (int q = 0; q < nt; ++q)
-            for (int lane = 0; lane < 64; ++lane)
-              for (int j = 0; j < 8; ++j) {
-                const int quad = o / NS, rho = lane & 15, it = 4 * (o % NS) + rho % 4;
-                const int c = 16 * quad + 4 * (rho / 4) + it / NS;
-                int h, part;
-                hid_slot(bf, d.comp, q, lane >> 4, j, h, part);
-                wl[(((size_t)o * nt + q) * 64 + lane) * 8 + j] = bf_part(ws[(size_t)h * ncol + (size_t)(it % NS) * C + c], part);
-              }
+        std::vector<double> kcv, ws;
+        int NS = 0;
+        if (!layer_weights(stored, lv, x.W3, H, C, L, bf, kcv, ws, NS, &why)) { st = fail(MPIP_EINVAL, why); goto done; }
+        if (!bf && (st = put(std::vector<float>(kcv.begin(), kcv.end()), &d.kc[role])) != MPIP_OK) goto done;
+        const std::vector<uint16_t> wl = layer_operands(ws, NS, C, bf, rad, rh);
         if ((st = upload(m, wl, &d.wl[role])) != MPIP_OK) goto done;
       }
       // node matrices (k_mix.hip): MFMA A operand tiles of 16 rows x 32 k,
@@ -945,7 +1054,7 @@ mpip_status mpip_model_create(const mpip_hparams* hp, const float* w, size_t n, 
         for (int h = 0; h < H; ++h)
           for (int pi = 0; pi < NPl; ++pi)
             for (int c = 0; c < C; ++c) ws[(size_t)h * ncol + pi * C + c] = bfr(W3(h, lv[pi] * C + c));
-        if (d.comp) ws = to_basis(ws, ncol);
+        if (d.comp) ws = turned(rh.V, H, ws, ncol);
         std::vector<uint16_t> v((size_t)NPl * CN * nt * 64 * 8);
         for (int o = 0; o < NPl * CN; ++o)
           for (int q = 0; q < nt; ++q)
@@ -993,7 +1102,7 @@ mpip_status mpip_model_create(const mpip_hparams* hp, const float* w, size_t n, 
                   acc += ht1[(size_t)sp * C + c] * (double)W3(k, l * C + c) * (double)Wd[(size_t)c * nz_l + o];
                 all[(size_t)k * nz_l + o] = bfr((float)(acc * hp->inv_avg_neighbors));
               }
-            if (KH != H) all = to_basis(all, nz_l);
+            if (KH != H) all = turned(rh.V, H, all, nz_l);
             for (int k = 0; k < KH; ++k)
               for (int o = 0; o < nz_l; ++o) VW[((size_t)sp * KH + k) * nz_l + o] = (float)all[(size_t)k * nz_l + o];
           }
