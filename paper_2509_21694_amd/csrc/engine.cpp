@@ -454,6 +454,7 @@ struct RadialHost {
   std::vector<double> V;   // directions of the products with W3 (comp)
   int comp, kh1;
   int rn = kRadTab, crn = kRadTab;             // intervals
+  // the first layer's (empty: the products') and the products' table
   std::vector<uint32_t> rtab, crtab;           // BF16 form
   std::vector<float> rtab32, crtab32;          // FP32 form
 };
@@ -465,12 +466,14 @@ RadialHost radial_host(RadialHidden& rad, bool bf, bool first) {
   r.comp = basis.ok ? 1 : 0;
   r.kh1 = basis.ok32 && first ? 32 : H;
   if (bf) {
-    if (!r.comp || (first && r.kh1 == H)) {
-      r.rtab = radial_table(rad.W1, rad.W2, rad.nb, H, rad.rc, rad.p);
-      r.rtab.resize(r.rtab.size() + H, 0u);
-    }
-    if (r.comp) r.crtab = radial_table_comp(rad, r.V, false);
+    auto units = [&]() {
+      std::vector<uint32_t> t = radial_table(rad.W1, rad.W2, rad.nb, H, rad.rc, rad.p);
+      t.resize(t.size() + H, 0u);
+      return t;
+    };
+    r.crtab = r.comp ? radial_table_comp(rad, r.V, false) : units();
     if (r.kh1 == 32) r.rtab = radial_table_comp(rad, r.V, true);
+    else if (first && r.comp) r.rtab = units();
     return r;
   }
   auto table = [&](auto&& eval, int count, int* n) {
@@ -479,10 +482,13 @@ RadialHost radial_host(RadialHidden& rad, bool bf, bool first) {
     t.resize(t.size() + 4 * (size_t)count, 0.f);
     return t;
   };
+  if (!r.comp) {
+    r.crtab32 = table(rad, H, &r.crn);
+    r.rn = r.crn;
+    return r;
+  }
   // the species-factorised first layer reads all of a(d)
-  if (!r.comp || first) r.rtab32 = table(rad, H, &r.rn);
-  r.crn = r.rn;
-  if (!r.comp) return r;
+  if (first) r.rtab32 = table(rad, H, &r.rn);
   std::vector<double> a(H), da(H);
   r.crtab32 = table(
       [&](double x, double* b, double* db) {
@@ -780,6 +786,7 @@ mpip_status mpip_radial_operands(const mpip_hparams* hp, const float* w, size_t 
   if (!layer_weights(paths, live, W3, H, C, L, bf, kc, ws, NS, &why)) return fail(MPIP_EINVAL, why);
   const bool dir = set == 2 ? r.kh1 == 32 : r.comp != 0;
   const int nf = set == 2 ? r.kh1 : r.comp ? (bf ? 24 : 48) : H;
+  const bool first = set == 2 && (bf ? !r.rtab.empty() : !r.rtab32.empty());   // else the products' table
   info->functions = nf;
   info->directions = dir ? 1 : 0;
   info->intervals = bf ? kRadTab : (set == 2 ? r.rn : r.crn);
@@ -792,11 +799,12 @@ mpip_status mpip_radial_operands(const mpip_hparams* hp, const float* w, size_t 
       for (int f = 0; f < nf; ++f) {
         float* c = table + ((size_t)k * nf + f) * 4;
         if (!bf) {
-          std::memcpy(c, &(set == 2 || !r.comp ? r.rtab32 : r.crtab32)[((size_t)k * nf + f) * 4], 4 * sizeof(float));
+          std::memcpy(c, &(first ? r.rtab32 : r.crtab32)[((size_t)k * nf + f) * 4], 4 * sizeof(float));
           continue;
         }
         // interval rows of 64 hidden units, 32 directions, or 24 as 8 words a lane group
-        const uint32_t u = set == 2 || !dir ? r.rtab[(size_t)k * nf + f] : r.crtab[(size_t)k * 32 + 8 * (f % 4) + f / 4];
+        const uint32_t u = first ? r.rtab[(size_t)k * nf + f]
+                           : dir ? r.crtab[(size_t)k * 32 + 8 * (f % 4) + f / 4] : r.crtab[(size_t)k * nf + f];
         c[1] = bf2f((uint16_t)(u >> 16));
         c[0] = bf2f((uint16_t)u) - (dir ? 0.5f * c[1] : 0.f);
         c[2] = c[3] = 0.f;
@@ -945,7 +953,8 @@ mpip_status mpip_model_create(const mpip_hparams* hp, const float* w, size_t n, 
       };
       if ((st = put(rh.rtab, &d.rtab)) != MPIP_OK || (st = put(rh.crtab, &d.crtab)) != MPIP_OK ||
           (st = put(rh.rtab32, &d.rtab32)) != MPIP_OK || (st = put(rh.crtab32, &d.crtab32)) != MPIP_OK) goto done;
-      if (!rh.comp) { d.crtab = d.rtab; d.crtab32 = d.rtab32; }
+      if (!d.rtab) d.rtab = d.crtab;
+      if (!d.rtab32) d.rtab32 = d.crtab32;
       for (int role = 0; role < 2; ++role) {
         const std::vector<int>& lv = live[role];
         const int NPl = (int)lv.size();

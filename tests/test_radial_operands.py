@@ -67,16 +67,19 @@ def _case(scale, layer, hp=None):
 
 @pytest.mark.parametrize("prec", ["fp32", "bf16"])
 @pytest.mark.parametrize("layer,kind", [(1, 0), (1, 1), (1, 2), (2, 0), (3, 1)])
-@pytest.mark.parametrize("scale", [1.0, 4.0])
+@pytest.mark.parametrize("scale", [1.0, 1.5, 4.0])
 def test_tables_and_weights(prec, layer, kind, scale):
     M = _lib()
     hp, blob, lay = _case(scale, layer)
     direc, turn, table, wts = M.radial_operands(hp, blob, layer, prec, kind)
     n = turn.shape[1]
     if scale == 4.0 or (kind == 2 and prec == "fp32"):
-        assert not direc and n == hp.radial_hidden and np.array_equal(turn, np.eye(n))
+        assert not direc
+    if not direc:
+        assert scale > 1.0 or kind == 2
+        assert n == hp.radial_hidden and np.array_equal(turn, np.eye(n))
     else:
-        assert direc and n == (32 if kind == 2 else 24 if prec == "bf16" else 48)
+        assert n == (32 if kind == 2 else 24 if prec == "bf16" else 48)
         assert np.abs(turn.T @ turn - np.eye(n)).max() < 1e-12
     # distances from 0.1 A, off the knots (tau between 0 and 1)
     d = 0.1 + (hp.r_cut - 0.1) * (np.arange(4000) + 0.37) / 4000
@@ -84,12 +87,13 @@ def test_tables_and_weights(prec, layer, kind, scale):
     b, db = functions(table, d, hp.r_cut)
     scale_a, scale_d = np.abs(a @ turn).max(), np.abs(da @ turn).max()
     if prec == "bf16":
-        # a line through BF16 values and increments (each to U), off by h^2/8 |b''|, its slope by h/2 |b''|;
+        # a line from the knot before, at most h |db| away, BF16 value and increment (each to U), off by h^2/8 |b''|,
+        # its slope by h/2 |b''|;
         # |b''| over an interval from da/dd at the sample and h to either side, twice that for its change
         h = hp.r_cut / table.shape[0]
         curve = 2 * np.maximum(np.abs(_oracle_a(d + h, lay, hp)[1] - da), np.abs(_oracle_a(d - h, lay, hp)[1] - da)) / h
         b2 = curve if not direc else np.repeat(np.linalg.norm(curve, axis=1)[:, None], n, axis=1)
-        assert np.all(np.abs(b - a @ turn) <= U * (1 + U) * (np.abs(a @ turn) + h * np.abs(da @ turn)) + h * h * b2)
+        assert np.all(np.abs(b - a @ turn) <= U * (1 + U) * (np.abs(a @ turn) + 2 * h * np.abs(da @ turn)) + h * h * b2)
         assert np.all(np.abs(db - da @ turn) <= U * np.abs(da @ turn) + (1 + U) * h / 2 * b2)
     else:                # interpolated to 1e-8 and 1e-7 of the maxima, FP32 coefficients (2^-24 each, four of them)
         assert np.abs(b - a @ turn).max() <= (1e-8 + 2.0 ** -22) * scale_a
