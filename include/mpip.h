@@ -63,23 +63,24 @@ typedef enum {
                               cubic per interval of [0, r_c], FP32 coefficients, intervals
                               doubled until a and da/dr are interpolated to 1e-8 and 1e-7 of
                               their maxima (the MLP in FP32 is 2e-7 off); past the first layer in
-                              the 48 directions of a that matter, when the rest is below FP32   */
-  MPIP_BF16_MIXED = 1      /* radial layer and channel mixing as BF16 MFMA with FP32 accumulation.
-                              a(r) is read from a per-layer table (built at model creation in
-                              FP64 from the FP32 weights: 4096 intervals over [0, r_c], BF16
-                              value and increment per interval, linear interpolation, the
-                              interval's slope as da/dr), in the 24 (first layer 32) directions
-                              of a that matter when the rest is below BF16's rounding, else in
-                              all 64 hidden units.  In the specialised first and last layers (64
-                              or 128 channels) the tensor-product contractions run on BF16 MFMA
-                              with BF16 operands and FP32 accumulation (first layer: Q = a (x) YC
-                              and its adjoint; last layer: X = ht . YC, dE/dYC, dE/dr and the
+                              48 directions of a, when what that leaves out is at every distance
+                              at most 2^-22 of |a(r)| and 2^-20 of |da/dr| there                */
+  MPIP_BF16_MIXED = 1      /* radial layer and channel mixing as BF16 MFMA with FP32
+                              accumulation. a(r) is read from a per-layer table (built at model
+                              creation in FP64 from the FP32 weights: 4096 intervals over [0,
+                              r_c], BF16 value and increment per interval, linear interpolation,
+                              the interval's slope as da/dr), in 24 directions of a when the
+                              rest is at every distance at most 2^-9 of |a(r)| and 2^-8 of
+                              |da/dr| there (first layer: 32, 2^-12 and 2^-10), else in all 64
+                              hidden units. In the specialised first and last layers (64 or 128
+                              channels) the tensor-product contractions run on BF16 MFMA with
+                              BF16 operands and FP32 accumulation (first layer: Q = a (x) YC and
+                              its adjoint; last layer: X = ht . YC, dE/dYC, dE/dr and the
                               sender-side pull), and the last layer's ht and per-edge messages
                               are stored in BF16; all other layers form the tensor product on
-                              the VALU in FP32.
-                              Geometry (harmonics) in FP32; r_e is the FP64 displacement
-                              rounded to FP32 (also in the virial); energy, force and virial
-                              sums in FP64                                                        */
+                              the VALU in FP32. Geometry (harmonics) in FP32; r_e is the FP64
+                              displacement rounded to FP32 (also in the virial); energy, force
+                              and virial sums in FP64                                            */
 } mpip_precision;
 
 typedef struct {

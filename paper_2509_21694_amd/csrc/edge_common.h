@@ -302,7 +302,7 @@ struct Parts {
 // 430 -> 386; FP32 499 -> 414 and 822 -> 623 us.
 //   FP32: five chunks.  Lane group g holds directions 4 g .. 4 g + 3 of each of
 //   the groups A, B, C (0.., 16.., 32..).  A takes all six products that reach
-//   2^-24 of it, B (2^-7 of A at most) three, C (2^-15) one:
+//   2^-24 of it, B (at most 2^-5 of a(d): radial_basis) three, C (2^-13) one:
 //     W1A (A1, A2)   W2A (A1, A2)   W1A A3, W3A A1   W1B (B1, B2)   W2B B1, W1C C1.
 template <int F>
 struct HidForm {

@@ -141,21 +141,21 @@ struct RadialHidden {
 };
 
 // Directions of a radial layer: a(d) = V b(d) with V orthogonal, the columns
-// by falling size of b over [0, r_c], value and derivative on one scale
-// (singular vectors of 512 samples of both; BF16: samples weighted with
-// d^1.25, about as the neighbours are distributed).  a(d) is a smooth curve, so
-// b falls fast: for weights of fan-in scale to 1e-3 of its largest by the 16th
-// of the 64, 6e-7 by the 32nd, 6e-10 by the 48th (BF16's: 5e-4 by the 24th).
+// by falling size of b over [0, r_c] (singular vectors of 512 samples of value
+// and derivative, each sample relative to its own size: what is left out is
+// then as small beside a(d) where a(d) is small, towards the cutoff, as where
+// it is large, at distances where no neighbours are).  a(d) is a smooth curve,
+// so b falls fast.
 // ok: what the compressed forms leave out (edge_common.h: HidForm) is below
-// the forms' own rounding, in the value and in the derivative:
-//   BF16: directions from 24 on, at most 2^-10 of the largest |a| and 2^-8 of
-//     the largest |da/dd| anywhere (both at small d; the operands are rounded
-//     to 2^-9).  W3 in these directions, the first eight in two parts, gives
-//     R of the BF16 W3 to 1.3e-4 and dR/dd to 1.5e-4 on average over a shell of
-//     neighbours (rounding W3 itself: 5e-4 to 1.4e-3).  The first layer's Q has
-//     room for 32: 2^-12 and 2^-10 from there on;
-//   FP32: directions from 48 on 2^-27 and 2^-25, those from 32 on, in one BF16
-//     part, 2^-17 and 2^-15, those from 16 on, in two, 2^-8 and 2^-7.
+// the forms' own rounding at every sample, relative to |a| and |da/dd| there:
+//   BF16: directions from 24 on, at most 2^-9 of |a(d)| and 2^-8 of |da/dd|.
+//     The first layer's Q has room for 32: 2^-12 and 2^-10 from there on;
+//   FP32: directions from 48 on and what the missing products of BF16 parts
+//     would add in those before (about 2^-9 of 32..47, 2^-17 of 16..31, 2^-25
+//     of the first 16), at most 2^-22 and 2^-20 (the MLP in FP32: 2e-7 off).
+// Of 40 random weight sets each: fan-in scale 7e-4 and 2e-3 at most (BF16, 24),
+// 4e-5 and 1e-4 (32), 1.6e-7 and 3.6e-7 (FP32), all kept; W1 x 1.25 BF16 all,
+// FP32 two thirds; W1 x 1.5 two thirds and a twentieth; W1 x 2 none.
 struct RadialBasis {
   std::vector<double> V;   // [H][H], direction k in column k
   bool ok;     // the compressed forms
@@ -163,26 +163,26 @@ struct RadialBasis {
 };
 RadialBasis radial_basis(RadialHidden& rad, bool bf) {
   const int H = rad.H, n = 512;
-  std::vector<double> A((size_t)n * H), D((size_t)n * H);
-  double sa = 0.0, sd = 0.0;
-  for (int k = 0; k < n; ++k) rad((k + 0.5) / n, &A[(size_t)k * H], &D[(size_t)k * H]);
-  auto weight = [&](int k) { return bf ? std::pow((k + 0.5) / n, 1.25) : 1.0; };
-  for (int k = 0; k < n; ++k)
+  std::vector<double> A((size_t)n * H), D((size_t)n * H), na(n, 0.0), nd(n, 0.0);
+  RadialBasis r{std::vector<double>((size_t)H * H, 0.0), true, false};
+  for (int k = 0; k < n; ++k) {
+    rad((k + 0.5) / n, &A[(size_t)k * H], &D[(size_t)k * H]);
     for (int h = 0; h < H; ++h) {
-      const double u = weight(k) * A[(size_t)k * H + h], v = weight(k) * D[(size_t)k * H + h];
-      sa += u * u;
-      sd += v * v;
+      na[k] += A[(size_t)k * H + h] * A[(size_t)k * H + h];
+      nd[k] += D[(size_t)k * H + h] * D[(size_t)k * H + h];
     }
-  RadialBasis r{std::vector<double>((size_t)H * H, 0.0), sa > 0.0 && sd > 0.0 && std::isfinite(sa) && std::isfinite(sd), false};
+    na[k] = std::sqrt(na[k]);
+    nd[k] = std::sqrt(nd[k]);
+    r.ok = r.ok && na[k] > 0.0 && nd[k] > 0.0 && std::isfinite(na[k]) && std::isfinite(nd[k]);
+  }
   for (int h = 0; h < H; ++h) r.V[(size_t)h * H + h] = 1.0;
   if (!r.ok) return r;
   // R of a QR factorisation (modified Gram-Schmidt) of the 2 n scaled rows; column-major
   std::vector<double> M((size_t)H * 2 * n), U((size_t)H * H, 0.0);
-  const double fa = 1.0 / std::sqrt(sa), fd = 1.0 / std::sqrt(sd);
   for (int h = 0; h < H; ++h)
     for (int k = 0; k < n; ++k) {
-      M[(size_t)h * 2 * n + k] = fa * weight(k) * A[(size_t)k * H + h];
-      M[(size_t)h * 2 * n + n + k] = fd * weight(k) * D[(size_t)k * H + h];
+      M[(size_t)h * 2 * n + k] = A[(size_t)k * H + h] / na[k];
+      M[(size_t)h * 2 * n + n + k] = D[(size_t)k * H + h] / nd[k];
     }
   auto dot = [](const double* x, const double* y, int m) {
     double t = 0.0;
@@ -236,26 +236,33 @@ RadialBasis radial_basis(RadialHidden& rad, bool bf) {
   std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return size[x] > size[y]; });
   for (int k = 0; k < H; ++k)
     for (int h = 0; h < H; ++h) r.V[(size_t)h * H + k] = W[(size_t)order[k] * H + h];
-  // largest norm over d of the part of a function in directions k0 on
-  auto part = [&](const std::vector<double>& f, int k0) {
-    double most = 0.0;
-    for (int k = 0; k < n; ++k) {
-      double t = 0.0;
-      for (int q = k0; q < H; ++q) {
-        double b = 0.0;
-        for (int h = 0; h < H; ++h) b += r.V[(size_t)h * H + q] * f[(size_t)k * H + h];
-        t += b * b;
+  // b and db/dd, squared, at the samples
+  std::vector<double> B((size_t)n * H), E((size_t)n * H);
+  for (int k = 0; k < n; ++k)
+    for (int q = 0; q < H; ++q) {
+      double u = 0.0, v = 0.0;
+      for (int h = 0; h < H; ++h) {
+        u += r.V[(size_t)h * H + q] * A[(size_t)k * H + h];
+        v += r.V[(size_t)h * H + q] * D[(size_t)k * H + h];
       }
-      most = std::max(most, t);
+      B[(size_t)k * H + q] = u * u;
+      E[(size_t)k * H + q] = v * v;
     }
-    return std::sqrt(most);
+  // at every sample, 2^left[q / 16] of the directions from k0 on is at most 2^ea and 2^ed of the whole
+  auto below = [&](int k0, const int (&left)[4], int ea, int ed) {
+    for (int k = 0; k < n; ++k) {
+      double u = 0.0, v = 0.0;
+      for (int q = k0; q < H; ++q) {
+        const double f = std::ldexp(1.0, 2 * left[std::min(q / 16, 3)]);
+        u += f * B[(size_t)k * H + q];
+        v += f * E[(size_t)k * H + q];
+      }
+      if (!(std::sqrt(u) <= std::ldexp(na[k], ea) && std::sqrt(v) <= std::ldexp(nd[k], ed))) return false;
+    }
+    return true;
   };
-  const double a0 = part(A, 0), d0 = part(D, 0);
-  auto below = [&](int k0, int ea, int ed) {
-    return part(A, k0) <= std::ldexp(a0, ea) && part(D, k0) <= std::ldexp(d0, ed);
-  };
-  r.ok32 = bf && H >= 32 && below(32, -12, -10);
-  r.ok = bf ? H >= 24 && below(24, -10, -8) : H >= 48 && below(16, -8, -7) && below(32, -17, -15) && below(48, -27, -25);
+  r.ok32 = bf && H >= 32 && below(32, {0, 0, 0, 0}, -12, -10);
+  r.ok = bf ? H >= 24 && below(24, {0, 0, 0, 0}, -9, -8) : H >= 48 && below(0, {-25, -17, -9, 0}, -22, -20);
   return r;
 }
 
@@ -279,13 +286,13 @@ void hid_slot(bool bf, bool comp, int q, int g, int j, int& h, int& part) {
   }
 }
 int hid_tiles(bool bf, bool comp) { return comp ? (bf ? 1 : 5) : (bf ? 2 : 6); }
-// BF16 part of a weight
+// BF16 part of a weight (of its FP64 value: a turned weight's third part
+// reaches past FP32's rounding, which is the same for every edge)
 uint16_t bf_part(double w, int part) {
-  float v = (float)w;
-  uint16_t u = f2bf(v);
+  uint16_t u = f2bf((float)w);
   for (int k = 0; k < part; ++k) {
-    v -= bf2f(u);
-    u = f2bf(v);
+    w -= bf2f(u);
+    u = f2bf((float)w);
   }
   return u;
 }

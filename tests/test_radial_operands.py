@@ -88,8 +88,8 @@ def test_tables_and_weights(prec, layer, kind, scale):
     scale_a, scale_d = np.abs(a @ turn).max(), np.abs(da @ turn).max()
     if prec == "bf16":
         # a line from the knot before, at most h |db| away, BF16 value and increment (each to U), off by h^2/8 |b''|,
-        # its slope by h/2 |b''|;
-        # |b''| over an interval from da/dd at the sample and h to either side, twice that for its change
+        # its slope by h/2 |b''|; |b''| over an interval from da/dd at the sample and h to either side, twice that for
+        # its change
         h = hp.r_cut / table.shape[0]
         curve = 2 * np.maximum(np.abs(_oracle_a(d + h, lay, hp)[1] - da), np.abs(_oracle_a(d - h, lay, hp)[1] - da)) / h
         b2 = curve if not direc else np.repeat(np.linalg.norm(curve, axis=1)[:, None], n, axis=1)
@@ -113,6 +113,38 @@ def test_tables_and_weights(prec, layer, kind, scale):
         # W3 takes one of the two neighbouring BF16 values (2 U at most), is turned, and rounded again
         size = np.linalg.norm(columns(hp, lay, layer, prec, kind == 1), axis=0)
         assert np.all(np.linalg.norm(wts - ref, axis=0) <= (2 * U + U * (1 + 2 * U)) * size)
+
+
+@pytest.mark.parametrize("prec", ["fp32", "bf16"])
+@pytest.mark.parametrize("scale", [1.0, 1.25, 1.5])
+@pytest.mark.parametrize("layer,kind", [(1, 2), (2, 0), (3, 1)])
+def test_directions_hold_at_every_distance(prec, layer, kind, scale):
+    """What the directions leave out of a(d) and da/dd is small beside a(d) and da/dd at the same distance, from 0.1 A
+    to one per cent below the cutoff (where a(d) is 1e-5 of its largest): 2^-9 and 2^-8 of them in the BF16 form (of
+    the first layer's 32: 2^-12 and 2^-10), 2^-22 and 2^-20 in the FP32 form, there with what the directions that
+    have one (from the 32nd on) or two BF16 parts (from the 16th) lose, half a unit roundoff U of a part on average.
+    To that the rounding of the table.  Distances at which the tables are exact but for that: the FP32 form's knots,
+    the middles of the BF16 form's intervals (the increment is h b' to h^2 / 24 of the third derivative, below
+    2^-12 b' here)."""
+    M = _lib()
+    hp, blob, lay = _case(scale, layer)
+    direc, turn, table, _ = M.radial_operands(hp, blob, layer, prec, kind)
+    if not direc:
+        assert scale > 1.0 or (kind == 2 and prec == "fp32")
+        return
+    n = table.shape[0]
+    d = (np.arange(n // 50 + 1, int(0.99 * n), max(1, n // 1500)) + (0.5 if prec == "bf16" else 0.0)) * hp.r_cut / n
+    a, da = _oracle_a(d, lay, hp)
+    b, db = functions(table, d, hp.r_cut)
+    rest, drest = (2.0 ** -12, 2.0 ** -10) if kind == 2 else (2.0 ** -9, 2.0 ** -8)
+    lose, rnd = 0.0, U
+    if prec == "fp32":
+        rest, drest, lose, rnd = 2.0 ** -22, 2.0 ** -20, U / 2, 2.0 ** -23
+    for got, ref, most in ((b, a, rest + rnd), (db, da, drest + rnd + (2.0 ** -12 if prec == "bf16" else 0.0))):
+        parts = lose * np.linalg.norm(got[:, 32:], axis=1) + lose * U * np.linalg.norm(got[:, 16:32], axis=1)
+        off = np.hypot(np.linalg.norm(ref - got @ turn.T, axis=1), parts) / np.linalg.norm(ref, axis=1)
+        print(prec, layer, kind, scale, "worst", off.max(), "at", d[off.argmax()], "bound", most)
+        assert off.max() <= most
 
 
 def test_rejects_bad_arguments():
