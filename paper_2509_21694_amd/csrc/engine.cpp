@@ -444,6 +444,26 @@ std::vector<float> radial_table32(Eval&& eval, int H, double rc) {
   return t;
 }
 
+// Columns k0 .. k0 + m of V (m a power of two) turned among themselves by the
+// Hadamard matrix: in the order of size the first is 0.85 of a(d) and more, and
+// its BF16 rounding has one sign for all edges of a distance.  Force error of
+// K = 2 (of the force RMS, mean over weight sets): the first layer's Q and P,
+// 128 channels 5.55e-3 -> 5.3e-3 (in 64 hidden units 5.1e-3); the products' (8 of
+// two parts, 16 of one) 32 channels 4.8e-3 -> 4.5e-3, 64 channels 4.6e-3 -> 4.75e-3,
+// 128 channels and deeper evaluations the same.
+void spread(std::vector<double>& V, int H, int k0, int m) {
+  std::vector<double> o(m);
+  for (int h = 0; h < H; ++h) {
+    double* v = &V[(size_t)h * H + k0];
+    for (int k = 0; k < m; ++k) {
+      o[k] = 0.0;
+      for (int q = 0; q < m; ++q) o[k] += __builtin_popcount(k & q) & 1 ? -v[q] : v[q];
+      o[k] /= std::sqrt((double)m);
+    }
+    std::copy(o.begin(), o.end(), v);
+  }
+}
+
 // V^T of an [H][cols] matrix
 std::vector<double> turned(const std::vector<double>& V, int H, const std::vector<double>& w, int cols) {
   std::vector<double> o((size_t)H * cols, 0.0);
@@ -458,7 +478,7 @@ std::vector<double> turned(const std::vector<double>& V, int H, const std::vecto
 // The radial functions of a layer as its kernels read them (LayerDev), every
 // table with a row of zeros at its end
 struct RadialHost {
-  std::vector<double> V;   // directions of the products with W3 (comp)
+  std::vector<double> V, V1;   // directions of the products with W3 (comp), of the first layer's Q (kh1 = 32)
   int comp, kh1;
   int rn = kRadTab, crn = kRadTab;             // intervals
   // the first layer's (empty: the products') and the products' table
@@ -473,13 +493,22 @@ RadialHost radial_host(RadialHidden& rad, bool bf, bool first) {
   r.comp = basis.ok ? 1 : 0;
   r.kh1 = basis.ok32 && first ? 32 : H;
   if (bf) {
+    // within what the form treats alike: weights of two parts, of one, Q
+    if (r.kh1 == 32) {
+      r.V1 = r.V;
+      spread(r.V1, H, 0, 32);
+    }
+    if (r.comp) {
+      spread(r.V, H, 0, 8);
+      spread(r.V, H, 8, 16);
+    }
     auto units = [&]() {
       std::vector<uint32_t> t = radial_table(rad.W1, rad.W2, rad.nb, H, rad.rc, rad.p);
       t.resize(t.size() + H, 0u);
       return t;
     };
     r.crtab = r.comp ? radial_table_comp(rad, r.V, false) : units();
-    if (r.kh1 == 32) r.rtab = radial_table_comp(rad, r.V, true);
+    if (r.kh1 == 32) r.rtab = radial_table_comp(rad, r.V1, true);
     else if (first && r.comp) r.rtab = units();
     return r;
   }
@@ -800,7 +829,7 @@ mpip_status mpip_radial_operands(const mpip_hparams* hp, const float* w, size_t 
   info->columns = set == 2 ? 0 : NS * C;
   if (turn)
     for (int h = 0; h < H; ++h)
-      for (int k = 0; k < nf; ++k) turn[(size_t)h * nf + k] = dir ? r.V[(size_t)h * H + k] : (h == k ? 1.0 : 0.0);
+      for (int k = 0; k < nf; ++k) turn[(size_t)h * nf + k] = dir ? (set == 2 ? r.V1 : r.V)[(size_t)h * H + k] : (h == k ? 1.0 : 0.0);
   if (table)
     for (int k = 0; k < info->intervals; ++k)
       for (int f = 0; f < nf; ++f) {
@@ -1118,7 +1147,7 @@ mpip_status mpip_model_create(const mpip_hparams* hp, const float* w, size_t n, 
                   acc += ht1[(size_t)sp * C + c] * (double)W3(k, l * C + c) * (double)Wd[(size_t)c * nz_l + o];
                 all[(size_t)k * nz_l + o] = bfr((float)(acc * hp->inv_avg_neighbors));
               }
-            if (KH != H) all = turned(rh.V, H, all, nz_l);
+            if (KH != H) all = turned(rh.V1, H, all, nz_l);
             for (int k = 0; k < KH; ++k)
               for (int o = 0; o < nz_l; ++o) VW[((size_t)sp * KH + k) * nz_l + o] = (float)all[(size_t)k * nz_l + o];
           }

@@ -147,6 +147,23 @@ def test_directions_hold_at_every_distance(prec, layer, kind, scale):
         assert off.max() <= most
 
 
+@pytest.mark.parametrize("layer,kind,m", [(1, 2, 32), (2, 0, 8), (3, 1, 8)])
+def test_no_function_carries_the_rounding(layer, kind, m):
+    """BF16 form: a function that is most of a(d) would round as a whole, with one sign for all edges of a distance.
+    The direction that is most of it (the leading singular vector of the samples the directions come from, each
+    relative to its size) has the same share 1/m of each of m functions."""
+    M = _lib()
+    hp, blob, lay = _case(1.0, layer)
+    direc, turn, _, _ = M.radial_operands(hp, blob, layer, "bf16", kind)
+    assert direc
+    a, da = _oracle_a(hp.r_cut * (np.arange(512) + 0.5) / 512, lay, hp)
+    rows = np.concatenate([x / np.linalg.norm(x, axis=1, keepdims=True) for x in (a, da)])
+    lead = np.linalg.svd(rows, full_matrices=False)[2][0]
+    share = (turn.T @ lead) ** 2
+    assert np.abs(share[:m] - 1.0 / m).max() < 1e-9
+    assert m == len(share) or share[m:].max() < 1e-18
+
+
 def test_rejects_bad_arguments():
     M = _lib()
     hp, blob, _ = _case(1.0, 1)
