@@ -71,7 +71,7 @@ typedef enum {
                               r_c], BF16 value and increment per interval, linear interpolation,
                               the interval's slope as da/dr), in 24 directions of a when the
                               rest is at every distance at most 2^-9 of |a(r)| and 2^-8 of
-                              |da/dr| there (first layer: 32, 2^-12 and 2^-10), else in all 64
+                              |da/dr| there (first layer: 32, 2^-10 and 2^-9), else in all 64
                               hidden units. In the specialised first and last layers (64 or 128
                               channels) the tensor-product contractions run on BF16 MFMA with
                               BF16 operands and FP32 accumulation (first layer: Q = a (x) YC and
