@@ -89,17 +89,35 @@ std::vector<uint32_t> radial_table(const float* W1, const float* W2, int nb, int
 }
 
 // The second hidden layer a(d) of a radial MLP and its derivative, FP64 from
-// the FP32 weights
+// the FP32 weights.  Values on the grid of 1/8192 r_c, which all tables and
+// samples share, are kept: model creation evaluates each once for both forms.
 struct RadialHidden {
   const float *W1, *W2;
   int nb, H;
   double rc;
   int p;
-  std::vector<double> z1, dz1, z2, dz2;
+  std::vector<double> z1, dz1, z2, dz2, D2;   // D2: W2
   RadialHidden(const float* w1, const float* w2, int nb_, int H_, double rc_, int p_)
-      : W1(w1), W2(w2), nb(nb_), H(H_), rc(rc_), p(p_), z1(H_), dz1(H_), z2(H_), dz2(H_) {}
+      : W1(w1), W2(w2), nb(nb_), H(H_), rc(rc_), p(p_), z1(H_), dz1(H_), z2(H_), dz2(H_), D2(w2, w2 + (size_t)H_ * H_) {}
+  std::vector<double> grid;   // [8193][2][H]
+  std::vector<char> known;
   // at x = d / r_c
   void operator()(double x, double* a, double* da) {
+    const double t = x * 8192.0;
+    if (!(t >= 0.0 && t <= 8192.0 && t == std::floor(t))) { compute(x, a, da); return; }
+    if (known.empty()) {
+      known.assign(8193, 0);
+      grid.resize((size_t)8193 * 2 * H);
+    }
+    double* g = &grid[(size_t)t * 2 * H];
+    if (!known[(size_t)t]) {
+      compute(x, g, g + H);
+      known[(size_t)t] = 1;
+    }
+    std::copy(g, g + H, a);
+    std::copy(g + H, g + 2 * H, da);
+  }
+  void compute(double x, double* a, double* da) {
     const double pi = 3.14159265358979323846, pref = std::sqrt(2.0 / rc);
     const double ea = 0.5 * (p + 1) * (p + 2), eb = (double)p * (p + 2), ec = 0.5 * p * (p + 1);
     const double d = rc * x;
@@ -124,12 +142,13 @@ struct RadialHidden {
     }
     std::fill(z2.begin(), z2.end(), 0.0);
     std::fill(dz2.begin(), dz2.end(), 0.0);
+    double *y = z2.data(), *dy = dz2.data();
     for (int i = 0; i < H; ++i) {
       const double s = 1.0 / (1.0 + std::exp(-z1[i]));
       const double v = z1[i] * s, dv = dz1[i] * s * (1.0 + z1[i] * (1.0 - s));
       for (int h = 0; h < H; ++h) {
-        z2[h] += (double)W2[(size_t)i * H + h] * v;
-        dz2[h] += (double)W2[(size_t)i * H + h] * dv;
+        y[h] += D2[(size_t)i * H + h] * v;
+        dy[h] += D2[(size_t)i * H + h] * dv;
       }
     }
     for (int h = 0; h < H; ++h) {
@@ -212,7 +231,12 @@ RadialBasis radial_basis(RadialHidden& rad, bool bf) {
     for (int i = 0; i < H; ++i)
       for (int j = i + 1; j < H; ++j) {
         double *x = &U[(size_t)i * H], *y = &U[(size_t)j * H];
-        const double xx = dot(x, x, H), yy = dot(y, y, H), xy = dot(x, y, H);
+        double xx = 0.0, yy = 0.0, xy = 0.0;
+        for (int k = 0; k < H; ++k) {
+          xx += x[k] * x[k];
+          yy += y[k] * y[k];
+          xy += x[k] * y[k];
+        }
         if (std::fabs(xy) <= 1e-14 * std::sqrt(xx * yy)) continue;
         moved = true;
         const double z = (yy - xx) / (2.0 * xy);
@@ -240,17 +264,19 @@ RadialBasis radial_basis(RadialHidden& rad, bool bf) {
   for (int k = 0; k < H; ++k)
     for (int h = 0; h < H; ++h) r.V[(size_t)h * H + k] = W[(size_t)order[k] * H + h];
   // b and db/dd, squared, at the samples
-  std::vector<double> B((size_t)n * H), E((size_t)n * H);
-  for (int k = 0; k < n; ++k)
-    for (int q = 0; q < H; ++q) {
-      double u = 0.0, v = 0.0;
-      for (int h = 0; h < H; ++h) {
-        u += r.V[(size_t)h * H + q] * A[(size_t)k * H + h];
-        v += r.V[(size_t)h * H + q] * D[(size_t)k * H + h];
+  std::vector<double> B((size_t)n * H, 0.0), E((size_t)n * H, 0.0);
+  for (int k = 0; k < n; ++k) {
+    double *u = &B[(size_t)k * H], *v = &E[(size_t)k * H];
+    for (int h = 0; h < H; ++h)
+      for (int q = 0; q < H; ++q) {
+        u[q] += r.V[(size_t)h * H + q] * A[(size_t)k * H + h];
+        v[q] += r.V[(size_t)h * H + q] * D[(size_t)k * H + h];
       }
-      B[(size_t)k * H + q] = u * u;
-      E[(size_t)k * H + q] = v * v;
+    for (int q = 0; q < H; ++q) {
+      u[q] *= u[q];
+      v[q] *= v[q];
     }
+  }
   // at every sample, 2^left[q / 16] of the directions from k0 on is at most 2^ea and 2^ed of the whole
   auto below = [&](int k0, const int (&left)[4], int ea, int ed) {
     for (int k = 0; k < n; ++k) {
@@ -308,11 +334,8 @@ std::vector<uint32_t> radial_table_comp(RadialHidden& rad, const std::vector<dou
   std::vector<double> b((size_t)(2 * N + 1) * M), a(H), da(H);
   for (int k = 0; k <= 2 * N; ++k) {
     rad(0.5 * k / N, a.data(), da.data());
-    for (int q = 0; q < M; ++q) {
-      double t = 0.0;
-      for (int h = 0; h < H; ++h) t += V[(size_t)h * H + q] * a[h];
-      b[(size_t)k * M + q] = t;
-    }
+    for (int h = 0; h < H; ++h)
+      for (int q = 0; q < M; ++q) b[(size_t)k * M + q] += V[(size_t)h * H + q] * a[h];
   }
   std::vector<uint32_t> t((size_t)(N + 1) * M, 0u);
   for (int k = 0; k < N; ++k)
@@ -532,13 +555,13 @@ RadialHost radial_host(RadialHidden& rad, bool bf, bool first) {
   r.crtab32 = table(
       [&](double x, double* b, double* db) {
         rad(x, a.data(), da.data());
-        for (int k = 0; k < 48; ++k) {
-          b[k] = db[k] = 0.0;
-          for (int h = 0; h < H; ++h) {
+        std::fill(b, b + 48, 0.0);
+        std::fill(db, db + 48, 0.0);
+        for (int h = 0; h < H; ++h)
+          for (int k = 0; k < 48; ++k) {
             b[k] += r.V[(size_t)h * H + k] * a[h];
             db[k] += r.V[(size_t)h * H + k] * da[h];
           }
-        }
       },
       48, &r.crn);
   return r;
@@ -952,6 +975,7 @@ mpip_status mpip_model_create(const mpip_hparams* hp, const float* w, size_t n, 
       live[0].push_back(k);
       if (stored[k].l3 == 0) live[1].push_back(k);
     }
+    RadialHidden rad(x.W1, x.W2, nb, H, hp->r_cut, hp->envelope_p);
     for (int prec = 0; prec < 2; ++prec) {
       LayerDev& d = m->layers[prec][t - 1];
       const bool bf = prec == 1;
@@ -977,7 +1001,6 @@ mpip_status mpip_model_create(const mpip_hparams* hp, const float* w, size_t n, 
       };
       const int KC64 = bf ? 2 : 16;
       auto bfr = [&](float w) { return bf ? bf2f(f2bf(w)) : w; };   // a weight as the form holds it
-      RadialHidden rad(x.W1, x.W2, nb, H, hp->r_cut, hp->envelope_p);
       const RadialHost rh = radial_host(rad, bf, t == 1);
       d.comp = rh.comp;
       d.kh1 = rh.kh1;
