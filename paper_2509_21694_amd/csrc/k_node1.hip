@@ -257,6 +257,9 @@ __global__ __launch_bounds__(64 * kN1Waves) __attribute__((amdgpu_waves_per_eu(2
     lds_rows<MTC, KCC>(sU, KCC, 0, hv, lane, [&](int mt, f32x4 d) { hb[mt] = d; });
   };
   // P rows: D tile mt, lane (g, n) holds P index (KQ/4) g + 4 mt + r
+  // (lanes past the last atom repeat its values into its rows: a branch around
+  // the stores leaves the product's registers to be written again too early on
+  // the side that skips them, see tests/test_mfma_waits.py)
   auto pdst = [&](int lm) { return (__bf16*)a.P + ((int64_t)at * NLM + lm) * KQ + (KQ / 4) * g; };
   // zbar_0 blocks as B operands (scalars, then one gate block per l); P_0 is
   // formed from them at the end, after the last read of Q_0 (P overwrites Q)
@@ -319,9 +322,7 @@ __global__ __launch_bounds__(64 * kN1Waves) __attribute__((amdgpu_waves_per_eu(2
         for (int kc = 0; kc < KVC; ++kc) zb[kc] = kc < KCC ? tiles_to_op(hb, kc) : zb[kc - KCC];
         __bf16* dst = pdst(lm);
         PairStore ps;
-        lds_rows<MTP, KVC>(sP, KVC, 0, zb, lane, [&](int mt, f32x4 d) {
-          if (av) ps.put(mt, d, dst);
-        });
+        lds_rows<MTP, KVC>(sP, KVC, 0, zb, lane, [&](int mt, f32x4 d) { ps.put(mt, d, dst); });
       }
       // zbar of the gate block l: sum_m hbar_lm z_lm * sigmoid'
 #pragma unroll
@@ -344,9 +345,7 @@ __global__ __launch_bounds__(64 * kN1Waves) __attribute__((amdgpu_waves_per_eu(2
     stage_tiles<D::NP0>(sW, (const bf16x8*)a.vw[0] + (size_t)hf * D::NP0 * 64);
     lds_dma_sync();
     if (act)
-      lds_rows<MTP / 2, NZC>(sW, NZC, 0, z0b, lane, [&](int mt, f32x4 d) {
-        if (av) ps.put(hf * (MTP / 2) + mt, d, dst);
-      });
+      lds_rows<MTP / 2, NZC>(sW, NZC, 0, z0b, lane, [&](int mt, f32x4 d) { ps.put(hf * (MTP / 2) + mt, d, dst); });
   }
 }
 
