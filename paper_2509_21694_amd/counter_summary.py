@@ -13,7 +13,7 @@ are per SIMD (1024) or per CU (256) over that time:
   waves/SIMD  = 4 SQ_WAVE_CYCLES / (cycles * 1024)      (quad-cycles)
   wait        = SQ_WAIT_INST_ANY / SQ_WAVE_CYCLES
 
-usage: python -m paper_2509_21694_amd.counter_summary "command text" CSV [CSV ...]
+usage: python -m paper_2509_21694_amd.counter_summary [--title "title"] "command text" CSV [CSV ...]
        python -m paper_2509_21694_amd.counter_summary --trace "title" "command text" KERNEL_TRACE_CSV
 (the second form: per-kernel dispatch times from a --kernel-trace run)
 """
@@ -25,12 +25,13 @@ import re
 import sys
 
 KERNELS = collections.OrderedDict([
-    ("k_l2_adj", r"k_l2_adj<"), ("k_l2_msg", r"k_l2_msg<"), ("k_l2_msum", r"k_l2_msum<"),
+    ("k_l2_adj", r"k_l2_adj<"), ("k_l2_msg", r"k_l2_msg<"),
+    ("k_layer_fwd", r"k_layer_fwd<"), ("k_layer_bwd", r"k_layer_bwd<"),
     ("k_l1_fwd", r"k_l1_fwd<"), ("k_l1_bwd", r"k_l1_bwd<"), ("k_node1_fwd", r"k_node1_fwd<"),
-    ("k_node1_bwd", r"k_node1_bwd<"), ("k_nodeK", r"k_nodeK<"), ("k_nbr_w (count)", r"k_nbr_w<false>"),
+    ("k_node1_bwd", r"k_node1_bwd<"), ("k_nodeK", r"k_nodeK<"), ("k_mix_fwd", r"k_mix_fwd<"),
+    ("k_mix_bwd", r"k_mix_bwd<"), ("k_mix_last", r"k_mix_last<"), ("k_nbr_w (count)", r"k_nbr_w<false>"),
     ("k_nbr_w (fill)", r"k_nbr_w<true>"), ("k_nbr_rev", r"k_nbr_rev"), ("k_forces", r"k_forces"),
-    ("k_l2_msg32", r"k_l2_msg32<"), ("k_l2_adj32", r"k_l2_adj32<"), ("k_l2_msum32", r"k_l2_msum32<"),
-    ("k_gemm_lds", r"k_gemm_lds<"),
+    ("k_l2_msg32", r"k_l2_msg32<"), ("k_l2_msum32", r"k_l2_msum32<"),
 ])
 SIMD, CU, XCD = 1024, 256, 8
 
@@ -60,9 +61,12 @@ def collect(paths):
 
 
 def main():
-    cmd, paths = sys.argv[1], sys.argv[2:]
+    args, title = sys.argv[1:], "bulk1m (1,000,000 atoms, K = 2, l_max = 2, C = 128)"
+    if args[0] == "--title":
+        title, args = args[1], args[2:]
+    cmd, paths = args[0], args[1:]
     vals, meta = collect(paths)
-    print("# Per-kernel counters, bulk1m (1,000,000 atoms, K = 2, l_max = 2, C = 128)\n")
+    print(f"# Per-kernel counters, {title}\n")
     print("Commands (run from the repository root on one MI355X, `cd /tmp` first for rocprofv3):\n")
     print("```\n" + cmd + "\n```\n")
     defs = __doc__.split("over that time:")[1].split("usage:")[0].strip().splitlines()

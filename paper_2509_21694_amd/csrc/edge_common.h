@@ -53,17 +53,6 @@ struct PathList {
           }
     return P3{0, 0, 0};
   }
-  static constexpr int yc_off(int i) {
-    int o = 0;
-    for (int k = 0; k < i; ++k) o += (2 * get(k).l1 + 1) * (2 * get(k).l3 + 1);
-    return o;
-  }
-  static constexpr int cg_off(int i) {
-    int o = 0;
-    for (int k = 0; k < i; ++k) o += (2 * get(k).l1 + 1) * (2 * get(k).l2 + 1) * (2 * get(k).l3 + 1);
-    return o;
-  }
-  static constexpr int nyc() { return yc_off(count()); }
   static constexpr int nin() { return (KIND == KIND_ONLY || KIND == KIND_FIRST) ? 1 : (L + 1) * (L + 1); }
   static constexpr int nout() { return (KIND == KIND_ONLY || KIND == KIND_LAST) ? 1 : (L + 1) * (L + 1); }
 };
@@ -225,7 +214,6 @@ template <int PREC> struct Op;
 
 template <> struct Op<1> {  // BF16 operands, K = 32 per instruction
   typedef bf16x8 T;
-  static constexpr int KC64 = 2;   // k-chunks for K = 64
   __device__ static f32x4 mma(T a, T b, f32x4 c) { return mfma_bf16(a, b, c); }
   // operand of k-chunk kc from four D tiles (hidden 16*t + 4*g + r)
   __device__ static T from_tiles(const f32x4* t, int kc) {
@@ -234,37 +222,12 @@ template <> struct Op<1> {  // BF16 operands, K = 32 per instruction
     for (int j = 0; j < 8; ++j) v[j] = (__bf16)t[2 * kc + j / 4][j % 4];
     return v;
   }
-  __device__ static T load(const void* base, int idx) { return ((const T*)base)[idx]; }
-  // operand tile `tile` (64 lanes) of a packed array in global memory: the
-  // tile base is kept scalar and formed at its use, the lane adds a 32-bit offset
-  __device__ static T ldt(const void* base, int tile, int lane) {
-    const T* b = (const T*)base + (size_t)tile * 64;
-    asm volatile("" : "+s"(b));
-    return *(const T*)((const char*)b + (unsigned)lane * sizeof(T));
-  }
-  // operand of channels 32*kc + 8*g + j from an LDS row
-  __device__ static T from_row(const float* row, int kc, int g) {
-    T v;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = (__bf16)row[32 * kc + 8 * g + j];
-    return v;
-  }
-  static constexpr int kch(int K) { return K / 32; }
 };
 
 template <> struct Op<0> {  // FP32 operands, K = 4 per instruction
   typedef float T;
-  static constexpr int KC64 = 16;
   __device__ static f32x4 mma(T a, T b, f32x4 c) { return mfma_f32(a, b, c); }
   __device__ static T from_tiles(const f32x4* t, int q) { return t[q / 4][q % 4]; }
-  __device__ static T load(const void* base, int idx) { return ((const T*)base)[idx]; }
-  __device__ static T ldt(const void* base, int tile, int lane) {
-    const T* b = (const T*)base + (size_t)tile * 64;
-    asm volatile("" : "+s"(b));
-    return *(const T*)((const char*)b + (unsigned)lane * sizeof(T));
-  }
-  __device__ static T from_row(const float* row, int q, int g) { return row[4 * q + g]; }
-  static constexpr int kch(int K) { return K / 4; }
 };
 
 // MFMA operand of one hidden chunk (32 of the 64 units): BF16, or FP32 as

@@ -770,14 +770,6 @@ mpip_status upload(mpip_model* m, const std::vector<T>& v, const void** out) {
   return MPIP_OK;
 }
 
-// Pack a matrix generator f(lane, slot) into operand arrays.
-// bf16: 8 values per lane per chunk; f32: 1 value per lane per chunk.
-struct Packer {
-  std::vector<uint16_t> b;
-  std::vector<float> f;
-};
-
-
 }  // namespace
 
 extern "C" {
@@ -966,8 +958,6 @@ mpip_status mpip_model_create(const mpip_hparams* hp, const float* w, size_t n, 
     const LayerHost& x = lh[t - 1];
     const std::vector<Path> stored = layer_paths(t, L);
     const int PC = x.P * C;
-    auto W1 = [&](int n_, int h) { return x.W1[n_ * H + h]; };
-    auto W2 = [&](int a, int b) { return x.W2[a * H + b]; };
     auto W3 = [&](int h, int col) { return x.W3[(size_t)h * PC + col]; };
     // live path lists: role 0 (t < K): all stored; role 1 (t == K): l3 == 0
     std::vector<int> live[2];
@@ -979,27 +969,16 @@ mpip_status mpip_model_create(const mpip_hparams* hp, const float* w, size_t n, 
     for (int prec = 0; prec < 2; ++prec) {
       LayerDev& d = m->layers[prec][t - 1];
       const bool bf = prec == 1;
-      // generic packers
+      // BF16 operands, layout [outer][k][lane][8]
       auto pack = [&](int nchunk_outer, int nchunk_k, auto val, const void** dst) -> mpip_status {
-        // layout [outer][k][lane][8|1]
-        if (bf) {
-          std::vector<uint16_t> v((size_t)nchunk_outer * nchunk_k * 64 * 8);
-          for (int o = 0; o < nchunk_outer; ++o)
-            for (int k = 0; k < nchunk_k; ++k)
-              for (int lane = 0; lane < 64; ++lane)
-                for (int j = 0; j < 8; ++j)
-                  v[(((size_t)o * nchunk_k + k) * 64 + lane) * 8 + j] = f2bf(val(o, k, lane, j));
-          return upload(m, v, dst);
-        } else {
-          std::vector<float> v((size_t)nchunk_outer * nchunk_k * 64);
-          for (int o = 0; o < nchunk_outer; ++o)
-            for (int k = 0; k < nchunk_k; ++k)
-              for (int lane = 0; lane < 64; ++lane)
-                v[((size_t)o * nchunk_k + k) * 64 + lane] = val(o, k, lane, 0);
-          return upload(m, v, dst);
-        }
+        std::vector<uint16_t> v((size_t)nchunk_outer * nchunk_k * 64 * 8);
+        for (int o = 0; o < nchunk_outer; ++o)
+          for (int k = 0; k < nchunk_k; ++k)
+            for (int lane = 0; lane < 64; ++lane)
+              for (int j = 0; j < 8; ++j)
+                v[(((size_t)o * nchunk_k + k) * 64 + lane) * 8 + j] = f2bf(val(o, k, lane, j));
+        return upload(m, v, dst);
       };
-      const int KC64 = bf ? 2 : 16;
       auto bfr = [&](float w) { return bf ? bf2f(f2bf(w)) : w; };   // a weight as the form holds it
       const RadialHost rh = radial_host(rad, bf, t == 1);
       d.comp = rh.comp;
@@ -1507,7 +1486,7 @@ static void run_model(mpip_model* m, const Plan& p, char* w, const NbrBuffers& b
   const int kh1 = LD[0].kh1, KQ = kh1 * S;
   float* qp = p.o_qp ? (float*)(w + p.o_qp) : nullptr;
   FastArgs fa;
-  fa.n = N; fa.row_ptr = b.row_ptr; fa.e_src = b.e_src; fa.e_dst = b.e_dst; fa.e_rev = b.e_rev; fa.e_vec = b.e_vec; fa.capacity = max_edges;
+  fa.n = N; fa.row_ptr = b.row_ptr; fa.e_src = b.e_src; fa.e_rev = b.e_rev; fa.e_vec = b.e_vec; fa.capacity = max_edges;
   fa.status = b.status; fa.n_species = S;
   fa.inv_n = (float)hp.inv_avg_neighbors; fa.Q = qp; fa.P = qp; fa.g = g; fa.htbar = htbar;
   fa.msg = p.o_msg ? (void*)(w + p.o_msg) : nullptr;
@@ -1531,12 +1510,13 @@ static void run_model(mpip_model* m, const Plan& p, char* w, const NbrBuffers& b
   // the node work between them runs in the fused kernels of k_node1.hip
   const bool node1 = ht_bf16 && K == 2 && fast_layer(1) && fast_layer(2) && LD[0].n1_vwt[0] != nullptr;
   fa.htbar_bf16 = node1 ? 1 : 0;
-  // the last layer's node update fused with the message sum and its adjoint (BF16 form)
-  const bool nodeK = ht_bf16 && K >= 2 && fast_layer(K) && fa.msg && LD[K - 1].nk_dt != nullptr;
+  // the last layer's node update fused with the message sum and its adjoint
+  // (BF16 form: messages and weights exist wherever the last layer is specialised)
+  const bool nodeK = ht_bf16 && K >= 2 && fast_layer(K);
   // two specialised layers of the BF16 form: the last layer's edge gradients
   // go to the (then dead) message buffer and the first layer's adjoint
   // combines them
-  if (node1 && fa.msg) fa.g2p = (float4*)fa.msg;
+  if (node1) fa.g2p = (float4*)fa.msg;
   // the adjoint of the last layer by the kernels for any path set (always in
   // the FP32 form): it writes g on every edge it walks
   const bool layer_adj = !ht_bf16 || !fast_layer(K);
@@ -1598,15 +1578,14 @@ static void run_model(mpip_model* m, const Plan& p, char* w, const NbrBuffers& b
         fa.ht = ht; fa.A = A;
         fa.n = R(K - 1);   // sender-side: rows whose features feed the roots
         fa.row_end = root_end;
-        if (ht_bf16) launch_l2(prec, C, L, 4, fa, s);
+        if (ht_bf16) launch_l2(C, L, 4, fa, s);
         else launch_l2_32(C, L, 0, fa, s);
         fa.row_end = nullptr;
         fa.n = R(K);
-        if (!nodeK) {   // else the last-layer node pass sums the messages itself
+        if (!nodeK) {   // FP32 form; the BF16 form's node pass sums the messages itself
           T.end(s);
           T.begin("edge_sum_t" + std::to_string(t), s);
-          if (ht_bf16) launch_l2(prec, C, L, 5, fa, s);
-          else launch_l2_32(C, L, 1, fa, s);
+          launch_l2_32(C, L, 1, fa, s);
         }
       }
     } else {
@@ -1680,15 +1659,12 @@ static void run_model(mpip_model* m, const Plan& p, char* w, const NbrBuffers& b
         launch_l1(prec, L, false, fa, s);
       } else {
         fa.ht = ht; fa.Abar = A;
-        // the BF16 adjoint reads dA / n_avg, which the fused last-layer node
-        // kernel writes; after the generic node adjoint, scale here
-        if (!nodeK) launch_scale(A, (float)hp.inv_avg_neighbors, R(K) * (int64_t)C, s);
-        fa.n = R(K - 1);   // sender-side
+        fa.n = R(K - 1);   // sender-side; reads dA / n_avg, which k_nodeK wrote
         fa.row_end = root_end;
         // the walked prefix gets its gradient slots written; the rest of
         // those rows (receivers with dA = 0) must read as zero
         if (root_end && fa.g2p) zero_row_tails(fa.g2p, b.row_ptr, root_end, R(K - 1), N, max_edges, s);
-        launch_l2(prec, C, L, 3, fa, s);
+        launch_l2(C, L, 3, fa, s);
         fa.row_end = nullptr;
       }
     } else {

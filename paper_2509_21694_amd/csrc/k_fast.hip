@@ -15,7 +15,8 @@
 //
 // Last layer (only scalars out, paths (l, l, 0)), BF16 form, sender side:
 //   A_i[c] = sum_e sum_l R_e[l, c] <ht_j[l, :, c], YC_e[l, :]> / n_avg
-// as messages to the receiver's slots and their sum, and one adjoint kernel.
+// as messages to the receiver's slots (summed by the node kernel, k_node1.hip)
+// and one adjoint kernel.
 // The FP32 form's are in k_fast32.hip and k_layer.hip.
 #include "edge_common.h"
 
@@ -720,7 +721,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(HidForm
 //   m_e[c] = sum_l R_e[l, c] X_e[l, c],  X_e[l, c] = sum_m YC_e[lm] ht_j[lm, c]
 // (X a 16x16x16 MFMA of the row's transposed features) is
 // written in BF16 to the receiver-side slot M[rev(e')] in row i of the CSR.
-// A_i = sum_{e in row i} m_e / n_avg is then a contiguous segmented sum.
+// A_i = sum_{e in row i} m_e / n_avg is then a contiguous segmented sum (k_nodeK).
 template <int F, int C, int L, int NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4))) void k_l2_msg(FastArgs a) {
   constexpr int NLM = (L + 1) * (L + 1), NT = HidForm<F>::NT;
@@ -880,55 +881,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4)
   }
 }
 
-// A_i[c] = sum_{e in row i} M[e][c] / n_avg: one wave per row, C/8 lanes per
-// edge (8 channels each), 64/(C/8) edges per load, partial sums combined
-// across the lane groups at the end.
-template <int C>
-__global__ __launch_bounds__(256) void k_l2_msum(FastArgs a) {
-  constexpr int LPE = C / 8, EPI = 64 / LPE;
-  const int64_t i = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (fast_guard(a) || i >= a.n) return;
-  const int lane = threadIdx.x & 63, s = lane / LPE, c8 = lane % LPE;
-  const int e0 = a.row_ptr[i], e1 = a.row_ptr[i + 1];
-  const unsigned short* M = (const unsigned short*)a.msg + 8 * c8;
-  float acc[8];
-#pragma unroll
-  for (int q = 0; q < 8; ++q) acc[q] = 0.f;
-  int e = e0 + s;
-  for (; e + 3 * EPI < e1; e += 4 * EPI) {
-    uint4 u[4];
-#pragma unroll
-    for (int b = 0; b < 4; ++b) u[b] = *(const uint4*)(M + (int64_t)(e + b * EPI) * C);
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      const unsigned w[4] = {u[b].x, u[b].y, u[b].z, u[b].w};
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        acc[2 * t] += __uint_as_float(w[t] << 16);
-        acc[2 * t + 1] += __uint_as_float(w[t] & 0xffff0000u);
-      }
-    }
-  }
-  for (; e < e1; e += EPI) {
-    const uint4 u = *(const uint4*)(M + (int64_t)e * C);
-    const unsigned w[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      acc[2 * t] += __uint_as_float(w[t] << 16);
-      acc[2 * t + 1] += __uint_as_float(w[t] & 0xffff0000u);
-    }
-  }
-#pragma unroll
-  for (int q = 0; q < 8; ++q)
-#pragma unroll
-    for (int o = LPE; o < 64; o <<= 1) acc[q] += __shfl_xor(acc[q], o);
-  if (s == 0) {
-    float* dst = a.A + i * C + 8 * c8;
-    *(float4*)dst = make_float4(a.inv_n * acc[0], a.inv_n * acc[1], a.inv_n * acc[2], a.inv_n * acc[3]);
-    *(float4*)(dst + 4) = make_float4(a.inv_n * acc[4], a.inv_n * acc[5], a.inv_n * acc[6], a.inv_n * acc[7]);
-  }
-}
-
 // ============================================================ dispatch
 
 
@@ -967,7 +919,7 @@ void launch_l1(int prec, int L, bool fwd, const FastArgs& a, hipStream_t s) {
 
 // BF16 form, sender side: which = 3 the fused adjoint (3 waves per SIMD; all
 // hidden units: 2), 4 the messages (16 waves, 4 per SIMD sharing the LDS
-// weights), 5 their sum
+// weights)
 template <int F, int C, int L>
 static void l2_form(int which, const FastArgs& a, hipStream_t s) {
   if (which == 3) k_l2_adj<F, C, L, 4><<<l2_grid(a.n, 4, HidForm<F>::COMP ? 96 : 64), 64 * 4, 0, s>>>(a);
@@ -975,13 +927,11 @@ static void l2_form(int which, const FastArgs& a, hipStream_t s) {
 }
 template <int C, int L>
 static void l2_launch(int which, const FastArgs& a, hipStream_t s) {
-  if (which == 5) k_l2_msum<C><<<(unsigned)((a.n + 3) / 4), 256, 0, s>>>(a);
-  else if (a.comp) l2_form<3, C, L>(which, a, s);
+  if (a.comp) l2_form<3, C, L>(which, a, s);
   else l2_form<1, C, L>(which, a, s);
 }
 
-void launch_l2(int prec, int C, int L, int which, const FastArgs& a, hipStream_t s) {
-  (void)prec;   // BF16 form only (the FP32 form: launch_l2_32)
+void launch_l2(int C, int L, int which, const FastArgs& a, hipStream_t s) {
   if (C == 64 && L == 1) l2_launch<64, 1>(which, a, s);
   else if (C == 64 && L == 2) l2_launch<64, 2>(which, a, s);
   else if (C == 128 && L == 1) l2_launch<128, 1>(which, a, s);

@@ -39,42 +39,9 @@ __device__ __forceinline__ void store8_bf16(__bf16* dst, const float* v) {
   *(bf16x8*)dst = o;
 }
 
-// operand tile `tile` of a packed weight array: a uniform base plus a 32-bit
-// lane offset, so the address needs no per-lane 64-bit register
-__device__ __forceinline__ bf16x8 wtile(const bf16x8* W, int tile, int lane) {
-  const bf16x8* b = W + (size_t)tile * 64;
-  asm volatile("" : "+s"(b));   // keep the tile base scalar and computed at its use
-  return *(const bf16x8*)((const char*)b + (unsigned)lane * 16u);
-}
-
 template <typename F, int... Is>
 __device__ __forceinline__ void unroll_impl(F&& f, std::integer_sequence<int, Is...>) {
   (f(std::integral_constant<int, Is>{}), ...);
-}
-
-// D tiles mt = 0..MT-1 of W x B with W given as A-operand tiles
-// W[(mt0 + mt) * KS + k0 + kc] (kc < KC) and B as KC operands; the weights
-// are streamed from memory one M-tile ahead of their use and each finished
-// tile is handed to consume(mt, d), so only two tiles of weights are live.
-template <int MT, int KC, typename F>
-__device__ __forceinline__ void stream_rows(const bf16x8* W, int mt0, int KS, int k0, const bf16x8* B, int lane,
-                                           F&& consume) {
-  bf16x8 wb[2][KC];
-#pragma unroll
-  for (int kc = 0; kc < KC; ++kc) wb[0][kc] = wtile(W, mt0 * KS + k0 + kc, lane);
-  unroll_impl([&](auto mc) {
-    constexpr int mt = decltype(mc)::value;
-    __builtin_amdgcn_sched_barrier(0);
-    if constexpr (mt + 1 < MT) {
-#pragma unroll
-      for (int kc = 0; kc < KC; ++kc) wb[(mt + 1) & 1][kc] = wtile(W, (mt0 + mt + 1) * KS + k0 + kc, lane);
-    }
-    f32x4 d = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int kc = 0; kc < KC; ++kc) d = mfma_bf16(wb[mt & 1][kc], B[kc], d);
-    consume(mt, d);
-  }, std::make_integer_sequence<int, MT>{});
-  __builtin_amdgcn_sched_barrier(0);
 }
 
 }  // namespace

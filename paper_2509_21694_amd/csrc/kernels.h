@@ -222,7 +222,6 @@ struct FastArgs {
   int64_t n;
   const int32_t* row_ptr;
   const int32_t* e_src;
-  const int32_t* e_dst;  // receiver of each edge (edge-parallel adjoint a)
   const int32_t* e_rev;  // reverse edge (fused adjoint of the last layer)
   const float4* e_vec;
   int64_t capacity;
@@ -264,8 +263,8 @@ struct FastArgs {
 
 void launch_l1(int prec, int L, bool fwd, const FastArgs& a, hipStream_t s);
 // which (BF16 form): 3 the adjoint over the reverse edges, 4 the sender-side
-// messages, 5 their segmented sum into A
-void launch_l2(int prec, int C, int L, int which, const FastArgs& a, hipStream_t s);
+// messages (launch_nodeK sums them)
+void launch_l2(int C, int L, int which, const FastArgs& a, hipStream_t s);
 // last layer of the FP32 form, sender side (C = 64 or 128): which = 0 messages
 // (FP32, into msg), 1 their sum into A
 void launch_l2_32(int C, int L, int which, const FastArgs& a, hipStream_t s);
@@ -409,8 +408,6 @@ void add_energy_virial_launch(const double* e, const double* w, double* E, doubl
 void scatter_scalars_launch(const double* src, const int32_t* index, int64_t n, int64_t n_dst, double* dst,
                             hipStream_t s);
 void launch_zero(void* p, size_t bytes, hipStream_t s);
-// p[0 .. n-1] *= f
-void launch_scale(float* p, float f, int64_t n, hipStream_t s);
 // fill `bytes` (a multiple of 4) with a 32-bit pattern
 void launch_fill32(void* p, uint32_t value, size_t bytes, hipStream_t s);
 
