@@ -46,8 +46,9 @@ METRIC = "atom-steps/s (E+F) at 1M atoms, BF16 vs FP32 form on 1 GPU; force RMS 
 # MI355X published peaks.  The published FP32 vector peak (157.3 TFLOP/s)
 # counts packed FMA; every kernel here is compiled with packed FP32 off, so
 # the VALU ceiling used is the unpacked rate: 256 CUs x 4 SIMDs x 16 lanes x
-# 2 flop x 2.4 GHz = 78.6 TFLOP/s.
-PEAK = {"hbm": 8.0e12, "mfma_bf16": 2.5e15, "mfma_fp32": 157.3e12, "alu_fp32": 78.6e12}
+# 2 flop x 2.4 GHz = 78.6 TFLOP/s.  The FP32 form's products with weights run
+# as six products of BF16 parts on the BF16 MFMA: a sixth of its peak.
+PEAK = {"hbm": 8.0e12, "mfma_bf16": 2.5e15, "mfma_fp32": 2.5e15 / 6, "alu_fp32": 78.6e12}
 
 
 def workload(name):
@@ -60,12 +61,13 @@ def workload(name):
     raise SystemExit(f"unknown workload {name}")
 
 
-def phase_counts(hp, prec):
+def phase_counts(hp, prec, kh):
     """Algorithmic work of the step's phases, per directed edge and per atom,
     for the formulation they implement (live paths only, nothing recomputed
     is counted): {phase: (mfma_flop/edge, valu_flop/edge, bytes/edge,
     bytes/atom[, mfma_flop/atom])}.  Bytes are each array read or written
-    once per launch (unique bytes, not per-edge gathers)."""
+    once per launch (unique bytes, not per-edge gathers).  kh: functions of the
+    distance in the first layer's Q and P (64 hidden units, or 32 directions)."""
     C, L, H, nb, S = hp.channels, hp.l_max, hp.radial_hidden, hp.n_basis, hp.n_species
     nlm, P = (L + 1) ** 2, L + 1
     fb = 2 if prec == "bf16" else 4            # storage of Q/P and h~ in the form
@@ -73,18 +75,16 @@ def phase_counts(hp, prec):
     ev, src, grw = 16, 4, 32                   # e_vec, e_src, g read+write
     d = {
         # Q_i += a2 (x) YC over the row: layers 1-2 of the MLP and the outer product
-        "edge_fwd_t1": (2 * (mlp12 + H * nlm), 0.0, ev, 8 + nlm * 64 * S * fb),
+        "edge_fwd_t1": (2 * (mlp12 + H * nlm), 0.0, ev, 8 + nlm * kh * S * fb),
         # MLP adjoint through layers 2, 1; dE/da2 = P^T Ysel; dE/dYC = P a2
-        "edge_bwd_t1": (2 * (mlp12 + 2 * H * nlm), 0.0, ev + grw, 8 + nlm * 64 * S * fb),
+        "edge_bwd_t1": (2 * (mlp12 + 2 * H * nlm), 0.0, ev + grw, 8 + nlm * kh * S * fb),
         # last layer, sender side (both forms): messages with the full MLP,
         # X_l = <h~_j,l , YC_l> on MFMA (nlm MAC per channel), m = sum_l R_l X_l
         # on the VALU (P FMA per channel); h~_j read once per atom, e_vec, e_rev
-        # read per edge.  The per-edge messages this form writes (and the sum
-        # reads back) are not algorithmic bytes of the layer: they count in the
-        # measured traffic only
-        "edge_fwd_t2": (2 * (mlp12 + mlp3) + 2.0 * nlm * C, 2.0 * P * C, ev + src, 8 + nlm * C * fb),
+        # read and a message written per edge
+        "edge_fwd_t2": (2 * (mlp12 + mlp3) + 2.0 * nlm * C, 2.0 * P * C, ev + src + C * fb, 8 + nlm * C * fb),
         # A_i = sum over the row of the messages: C adds per edge; A_i (C FP32) written per atom
-        "edge_sum_t2": (0.0, 1.0 * C, 0, 8 + 4 * C),
+        "edge_sum_t2": (0.0, 1.0 * C, C * fb, 8 + 4 * C),
         # one fused adjoint over the reverse edges: the MLP adjoint, and
         # s_l = <h~_i,l , YC_l>, dYC and the pull (nlm MAC per channel each) on
         # MFMA; dR and R dA_j (P mul per channel each) on the VALU; e_rev read
@@ -92,20 +92,23 @@ def phase_counts(hp, prec):
         "edge_bwd_t2": (2 * (mlp12 + mlp3) + 6.0 * nlm * C, 2.0 * P * C, ev + 2 * src + grw,
                         8 + nlm * C * fb + C * 4 + nlm * C * fb),
     }
+    # node kernels between the two layers, forward and adjoint (one phase):
+    # z = Q (VW) and h~ = h W_up forward, h-bar = h~-bar W_up^T and P =
+    # z-bar (VW)^T backward; Q read, P written, h_0 (FP32) and h~ written, h~-bar
+    # read; z formed from Q again in the adjoint (BF16: Q read twice) or kept
+    # (FP32: z written and read)
+    KQ, zw = kh * S, C * (1 + L) + (nlm - 1) * C
+    zq, up = 2.0 * KQ * zw, 2.0 * nlm * C * C
+    qp = nlm * KQ * fb
+    # last-layer node update and its adjoint: h_0 read, dE/dA and E_i written;
+    # z_0 = W_down^T A and dE/dA = W_down z-bar on MFMA.  BF16: with the sum of
+    # the row's messages (C adds per edge, the messages read); FP32: A read
     if prec == "bf16":
-        # fused node kernels between the two layers, forward and adjoint
-        # (one phase): z = Q (VW) and h~ = h W_up forward, h-bar = h~-bar W_up^T
-        # and P = z-bar (VW)^T backward; Q read twice, P written, h_0 (FP32) and
-        # h~ (BF16) written, h~-bar (BF16) read
-        KQ = 64 * S
-        zq = 2.0 * KQ * (C * (1 + L) + (nlm - 1) * C)
-        up = 2.0 * nlm * C * C
-        d["node_fused"] = (0.0, 0.0, 0, 3 * nlm * KQ * 2 + 4 * C + 2 * nlm * C * 2, 2 * (zq + up))
-        # last-layer node update and its adjoint, with the message sum A_i =
-        # sum over the row of the messages (C adds per edge; the messages are
-        # intermediate, not algorithmic bytes): h_0 read, dE/dA written, E_i
-        # written; z_0 = W_down^T A and dE/dA = W_down z-bar on MFMA
-        d["node_last"] = (0.0, 1.0 * C, 0, 2 * 4 * C + 8, 2 * 2.0 * C * C)
+        d["node_fused"] = (0.0, 0.0, 0, 3 * qp + 4 * C + 2 * nlm * C * fb, 2 * (zq + up))
+        d["node_last"] = (0.0, 1.0 * C, C * fb, 2 * 4 * C + 8, 2 * 2.0 * C * C)
+    else:
+        d["node_fused"] = (0.0, 0.0, 0, 2 * qp + 4 * C + 2 * nlm * C * fb + 2 * zw * fb, 2 * (zq + up))
+        d["node_last"] = (0.0, 0.0, 0, 3 * 4 * C + 8, 2 * 2.0 * C * C)
     # neighbour list: positions and species read, the sorted copies, permutation
     # and row pointers written per atom; sender, shift, vector and reverse index
     # written per edge
@@ -115,8 +118,8 @@ def phase_counts(hp, prec):
     return d
 
 
-def kernel_roofline(name, t, hp, prec, n_edges, n_atoms):
-    counts = phase_counts(hp, prec)
+def kernel_roofline(name, t, hp, prec, n_edges, n_atoms, kh):
+    counts = phase_counts(hp, prec, kh)
     if name not in counts:
         return None
     fm, fv, be, ba, fma = (tuple(counts[name]) + (0.0,))[:5]
@@ -154,12 +157,12 @@ def measured_traffic(kernel_phase):
     return None
 
 
-def step_roofline(phases, steps, hp, n_edges, prec, n_atoms):
+def step_roofline(phases, steps, hp, n_edges, prec, n_atoms, kh):
     """Whole-step figure: sum over the step's phases of each one's roofline
     time (largest of MFMA, VALU and HBM time of its algorithmic work) over
     the measured step time.  Phases without an algorithmic count are listed
     with their time and a roof of zero."""
-    counts = phase_counts(hp, prec)
+    counts = phase_counts(hp, prec, kh)
     peak_m = PEAK["mfma_bf16"] if prec == "bf16" else PEAK["mfma_fp32"]
     per, roof_sum, t_sum = {}, 0.0, 0.0
     for k, (ms_total, calls) in phases.items():
@@ -177,12 +180,12 @@ def step_roofline(phases, steps, hp, n_edges, prec, n_atoms):
             "frac": round(roof_sum / t_sum, 4) if t_sum > 0 else None, "phases": per}
 
 
-def roofline_entry(phases, hp, n_edges, prec, n_atoms):
+def roofline_entry(phases, hp, n_edges, prec, n_atoms, kh):
     """Roofline of the edge kernel with the largest share of the step, plus
     the same figures for every specialised edge kernel."""
     per = {}
     for k, (ms_total, calls) in phases.items():
-        r = kernel_roofline(k, ms_total / calls * 1e-3, hp, prec, n_edges, n_atoms)
+        r = kernel_roofline(k, ms_total / calls * 1e-3, hp, prec, n_edges, n_atoms, kh)
         if r is not None:
             per[k] = r
     if not per:
@@ -367,10 +370,11 @@ def main():
             raise SystemExit(f"evaluation reported status {st}: {M.lib.mpip_last_error().decode()}")
         ms = (t1 - t0) / args.steps * 1e3
         log(f"{prec}: {ms:.3f} ms/step, {n_edges} edges")
+        kh = M.radial_operands(hp, blob, 1, prec, 2)[1].shape[1]
         r = {"ms_per_step": round(ms, 4), "value": round(N / (ms * 1e-3), 1), "n_edges": n_edges,
              "energy": E0, "phases_ms_per_step": {k: round(v[0] / args.steps, 4) for k, v in tm.items()},
-             "roofline": roofline_entry(tm, hp, n_edges, prec, N),
-             "step_roofline": step_roofline(tm, args.steps, hp, n_edges, prec, N),
+             "roofline": roofline_entry(tm, hp, n_edges, prec, N, kh),
+             "step_roofline": step_roofline(tm, args.steps, hp, n_edges, prec, N, kh),
              "errors_vs_fp64": errors}
         results[prec] = r
 
