@@ -134,7 +134,7 @@ __device__ __forceinline__ void stage_lds(T* dst, const void* src) {
 // directions of a(d) that matter (LayerDev::kh1), which halves Q and P, the
 // arrays that these kernels and the node kernels after them are bound by.
 // A million atoms, 3 species, l_max 2: forward 2.1 -> 1.2 ms, adjoint 2.7 -> 2.1;
-// the node kernels of 128 channels 1.63 -> 1.44 and 3.2 -> 2.2 ms.
+// the node kernels of 128 channels 1.63 -> 1.44 and 3.2 -> 1.8 ms.
 //
 // Forward: Q_i[q][k] = sum_e Ysel_e[q] a2_e[k], as D tiles (hidden 16 nt +
 // 4 g + r) x (q = 16 qt + lane % 16): the layer-2 activations in edges x

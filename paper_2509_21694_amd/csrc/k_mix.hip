@@ -18,8 +18,9 @@
 // The weights of a phase (a degree's W_up, its W_down) sit in LDS, shared by
 // the eight waves of a persistent workgroup.  Read from L2 instead, with one
 // wave per SIMD, each tile's loads waited for the stores before them (one
-// in-order counter), and the passes were bound by that latency.  Now: half by
-// the latency of the rows (65 % of the wave cycles wait), else by the passes
+// in-order counter), and the passes were bound by that latency.  Now: by the
+// latency of the rows, at 1.1 to 1.4 waves per SIMD (the LDS of the weights
+// allows no more; VALU 8 to 20 % and MFMA 2 to 9 % active), and by the passes
 // over Q, h, z and h~.
 //   103,635 atoms, FP32, 128 channels, l_max 2: forward 2.16 -> 0.88 ms,
 //   adjoint 2.06 -> 0.92 ms; 13,824 atoms, 64 channels: BF16 56 -> 41 and
