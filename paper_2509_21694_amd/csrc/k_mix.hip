@@ -19,9 +19,9 @@
 // the eight waves of a persistent workgroup.  Read from L2 instead, with one
 // wave per SIMD, each tile's loads waited for the stores before them (one
 // in-order counter), and the passes were bound by that latency.  Now: by the
-// latency of the rows, at 1.1 to 1.4 waves per SIMD (the LDS of the weights
-// allows no more; VALU 8 to 20 % and MFMA 2 to 9 % active), and by the passes
-// over Q, h, z and h~.
+// latency of the rows with few waves to cover it (13,824 atoms are 864 tiles:
+// 1.1 to 1.4 waves per SIMD, VALU 7 to 16 % and MFMA 2 to 11 % active), and by
+// the passes over Q, h, z and h~.
 //   103,635 atoms, FP32, 128 channels, l_max 2: forward 2.16 -> 0.88 ms,
 //   adjoint 2.06 -> 0.92 ms; 13,824 atoms, 64 channels: BF16 56 -> 41 and
 //   61 -> 48 us a layer, FP32 93 -> 50 and 93 -> 55; 4,096 atoms, FP32: 99 -> 44
